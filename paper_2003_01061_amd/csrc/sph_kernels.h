@@ -1095,6 +1095,27 @@ __global__ __launch_bounds__(BLOCK) void k_nbr_forces(
   }
 }
 
+// A position of u cells along an axis as whole cells and a fraction.  A
+// particle the caller put 2^30 cells or farther off the grid (of at most 2^29
+// cells) is taken to be that far off: its ranges end in the same border cells,
+// and a whole part plus a half chord stays an int.  A NaN stays one.
+__host__ __device__ __forceinline__ void cell_split(double u, int &whole, float &frac) {
+  constexpr double FAR = 1073741824.0;
+  u = u > FAR ? FAR : u;
+  u = u < -FAR ? -FAR : u;
+  const double f = __builtin_floor(u);
+  whole = (int)f;
+  frac = (float)(u - f);
+}
+// the cells [t0, t1] of a row of nc that a half chord of w cells about that position touches
+__host__ __device__ __forceinline__ void row_range(int whole, float frac, float w, int nc, int &t0, int &t1) {
+  w = __builtin_fminf(w, 1e9f);
+  t0 = whole + (int)__builtin_floorf(frac - w);
+  t1 = whole + (int)__builtin_floorf(frac + w);
+  t0 = t0 > 0 ? (t0 < nc - 1 ? t0 : nc - 1) : 0;
+  t1 = t1 > 0 ? (t1 < nc - 1 ? t1 : nc - 1) : 0;
+}
+
 // a word of a record that no kernel of the launch writes, at an address all
 // lanes of the wave share: one scalar load, and no vector register
 template <typename T>
@@ -1633,9 +1654,7 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
 #pragma unroll
           for (int a = 0; a < D; ++a) {
             const double lo = sload(Gr.lo[a]), inv = sload(Gr.inv_c[lv][a]);
-            const double u = (xd[a] - lo) * inv, f = __builtin_floor(u);
-            ic[a] = (int)f;
-            fr[a] = (float)(u - f);
+            cell_split((xd[a] - lo) * inv, ic[a], fr[a]);
             if (a > 0) {
               rlo[a] = coord(xd[a] - Rl, lo, inv, nc[a] - 1);
               rhi[a] = coord(xd[a] + Rl, lo, inv, nc[a] - 1);
@@ -1669,12 +1688,8 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
               const float dz = D == 3 ? gap(cz - ic[2], fr[2]) * c2 : 0.0f;
               const float w2 = R2 - dy * dy - dz * dz;
               if (!(w2 < 0.0f)) {
-                // half chord of the row
-                const float wu = __builtin_fminf(sqrt_(w2) * inv0 + 2e-5f, 1e9f);
-                int t0 = ic[0] + (int)__builtin_floorf(fr[0] - wu);
-                int t1 = ic[0] + (int)__builtin_floorf(fr[0] + wu);
-                t0 = t0 > 0 ? (t0 < nc[0] - 1 ? t0 : nc[0] - 1) : 0;
-                t1 = t1 > 0 ? (t1 < nc[0] - 1 ? t1 : nc[0] - 1) : 0;
+                int t0, t1;
+                row_range(ic[0], fr[0], sqrt_(w2) * inv0 + 2e-5f, nc[0], t0, t1);
                 // as cell_row
                 const uint32_t ry = (uint32_t)cy, rz = (uint32_t)cz;
                 const uint32_t rw = tiled ? (((rz >> 3) * nyt + (ry >> 3)) << 6) + ((rz & 7u) << 3) + (ry & 7u)
