@@ -2280,6 +2280,22 @@ struct OutHead {
 };
 constexpr size_t OUT_HEAD = 128;   // bytes; the rows start behind it
 static_assert(sizeof(OutHead) <= OUT_HEAD, "room for the flags");
+// The row of the particle with caller id o among n.  After a lost scan tile the
+// ids may be anything: the caller of the read-back learns of it from the flags
+// that come with the rows, so a row out of range is left out.
+template <int D>
+__host__ __device__ __forceinline__ void put_row(char *p, int n, uint32_t o, const double4 &x, int f, int rows,
+                                                 int features) {
+  if (o >= (uint32_t)n) return;
+  if (rows) {
+    double *r = reinterpret_cast<double *>(p) + 3 * (size_t)o;
+    r[0] = x.x;
+    r[1] = x.y;
+    r[2] = D == 3 ? x.z : 0.0;
+    p += 24 * (size_t)n;
+  }
+  if (features) reinterpret_cast<int32_t *>(p)[o] = f % MAXF;
+}
 template <int D>
 __global__ __launch_bounds__(BLOCK) void k_unsort(Batch B, int job, Parts s, const double4 *__restrict__ v,
                                                   int first, int n, char *__restrict__ out, int rows,
@@ -2291,17 +2307,8 @@ __global__ __launch_bounds__(BLOCK) void k_unsort(Batch B, int job, Parts s, con
   }
   const int k = (int)(blockIdx.x * BLOCK + threadIdx.x);
   if (k >= n) return;
-  const uint32_t o = s.oid[first + k];
-  char *p = out + OUT_HEAD;
-  if (rows) {
-    const double4 x = v[first + k];
-    double *r = reinterpret_cast<double *>(p) + 3 * (size_t)o;
-    r[0] = x.x;
-    r[1] = x.y;
-    r[2] = D == 3 ? x.z : 0.0;
-    p += 24 * (size_t)n;
-  }
-  if (features) reinterpret_cast<int32_t *>(p)[o] = s.f[first + k] % MAXF;
+  const double4 x = rows ? v[first + k] : make_double4(0.0, 0.0, 0.0, 0.0);
+  put_row<D>(out + OUT_HEAD, n, s.oid[first + k], x, features ? (int)s.f[first + k] : 0, rows, features);
 }
 
 }  // namespace sph
