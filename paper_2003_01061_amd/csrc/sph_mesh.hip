@@ -599,7 +599,6 @@ struct sph_batch {
   char *stage = nullptr;   // pinned memory of the read-back (need_stage)
   size_t stage_half = 0;
   hipEvent_t stage_ev[2] = {};
-  bool pair_normals = false;   // a resident 3D job has imported curves
   // captured step graphs: GRAPH_LONG steps and 2 steps (both start and end at
   // buffer parity 0); long runs replay the long one, so the gap the runtime
   // leaves between two graph launches comes once per GRAPH_LONG steps
@@ -745,12 +744,33 @@ struct sph_batch {
     return SPH_OK;
   }
 
-  // the blocks of G lanes per particle that cover the jobs `which` selects
+  // A set of resident jobs and the blocks that cover them with so many lanes per
+  // particle.  The neighbour kernels' sets hold the 3D jobs with imported curves
+  // apart (CURVED): their patches need the kernel with pair normals, and every
+  // job is to run the kernel it runs alone.
   struct SpanSet {
     Spans sp{};
     unsigned blocks = 0;
   };
-  enum { SPAN_ALL8 = 0, SPAN_ALL4, SPAN_ALL2, SPAN_ALL1, SPAN_SMALL, SPAN_LARGE, SPAN_SETS };
+  enum { SPAN_ALL8 = 0, SPAN_ALL4, SPAN_ALL1,   // every job
+         SPAN_NBR8, SPAN_NBR4, SPAN_NBR2, SPAN_SMALL, SPAN_LARGE,
+         SPAN_CURVED8, SPAN_CURVED4, SPAN_CURVED_SMALL, SPAN_CURVED_LARGE, SPAN_SETS };
+  int span_lanes(int k) const {
+    return k == SPAN_ALL8 || k == SPAN_NBR8 || k == SPAN_CURVED8   ? 8
+           : k == SPAN_ALL4 || k == SPAN_NBR4 || k == SPAN_CURVED4 ? 4
+           : k == SPAN_ALL1                                        ? 1
+           : k == SPAN_NBR2                                        ? 2
+           : k == SPAN_SMALL || k == SPAN_CURVED_SMALL             ? (D == 3 ? 8 : 4)
+                                                                   : (D == 3 ? 4 : 2);
+  }
+  bool in_span(int k, const HostJob &J) const {
+    if (k <= SPAN_ALL1) return true;
+    const bool curved = D == 3 && J.d_cpts != nullptr;
+    if (curved != (k >= SPAN_CURVED8)) return false;
+    if (k == SPAN_SMALL || k == SPAN_CURVED_SMALL) return small_job(J);
+    if (k == SPAN_LARGE || k == SPAN_CURVED_LARGE) return !small_job(J);
+    return true;
+  }
   SpanSet spans[SPAN_SETS];
   std::vector<Span> h_spans;   // host copy of the tables
   bool lists_long = false;     // a resident job has long lists
@@ -779,16 +799,14 @@ struct sph_batch {
     for (int j : order) lists_long = lists_long || long_lists(jobs[j]);
     h_spans.assign((size_t)SPAN_SETS * jcap, Span{});
     for (int k = 0; k < SPAN_SETS; ++k) {
-      const int lanes = k == SPAN_ALL8 ? 8 : k == SPAN_ALL4 ? 4 : k == SPAN_ALL2 ? 2 : k == SPAN_ALL1 ? 1
-                        : k == SPAN_SMALL ? (D == 3 ? 8 : 4) : (D == 3 ? 4 : 2);
-      const int pb = BLOCK / lanes;
+      const int pb = BLOCK / span_lanes(k);
       SpanSet &S = spans[k];
       S = SpanSet{};
       Span *t = h_spans.data() + (size_t)k * jcap;
       int first = 0;
       for (int j : order) {
         const HostJob &J = jobs[j];
-        if ((k != SPAN_SMALL && k != SPAN_LARGE) || (k == SPAN_SMALL) == small_job(J)) {
+        if (in_span(k, J)) {
           t[S.sp.count++] = Span{(int)S.blocks, j, first, first + J.n};
           S.blocks += (unsigned)((J.n + pb - 1) / pb);
         }
@@ -847,26 +865,32 @@ struct sph_batch {
   // 142 / 124; 2D, skin 0.8h, 4 against 2: 20,000 12 / 15, 250,000 32 / 35,
   // 500,000 54 / 54, 1,000,000 (compensated) 133 / 112.  (A mix's rebuilds, and
   // so the order of its sums, depend on all its jobs already.)
-  template <int DD, typename R, bool CMP, bool PN>
+  template <int DD, typename R, bool CMP>
   hipError_t launch_nbr_forces(const Batch &B, const Parts &s) {
     using R4 = typename Vec4<R>::T;
-    auto group = [&](auto kern, const SpanSet &S) {
-      return launch(KID_NBR_FORCES, kern, S.blocks, BLOCK, B, s, (const uint32_t *)cstart, 0, nbr, nnb,
-                    (R4 *)ap, dbg_gam, dbg_vt, s, S.sp);
+    auto group = [&](auto kern, int set) {
+      return launch(KID_NBR_FORCES, kern, spans[set].blocks, BLOCK, B, s, (const uint32_t *)cstart, 0, nbr, nnb,
+                    (R4 *)ap, dbg_gam, dbg_vt, s, spans[set].sp);
     };
     if (skin > 0.0) {
       if (hipError_t e = launch_build<DD>(B, s)) return e;
       if constexpr (DD == 3) {
-        if (n < 100000 || lists_long) return group(k_nbr_group<DD, R, true, CMP, 2, 8, PN>, spans[SPAN_ALL8]);
-        return group(k_nbr_group<DD, R, true, CMP, 2, 4, PN>, spans[SPAN_ALL4]);
+        if (n < 100000 || lists_long) {
+          if (hipError_t e = group(k_nbr_group<3, R, true, CMP, 2, 8, false>, SPAN_NBR8)) return e;
+          return group(k_nbr_group<3, R, true, CMP, 2, 8, true>, SPAN_CURVED8);
+        }
+        if (hipError_t e = group(k_nbr_group<3, R, true, CMP, 2, 4, false>, SPAN_NBR4)) return e;
+        return group(k_nbr_group<3, R, true, CMP, 2, 4, true>, SPAN_CURVED4);
       } else {
-        if (n < 500000) return group(k_nbr_group<DD, R, true, CMP, 2, 4, PN>, spans[SPAN_ALL4]);
-        return group(k_nbr_group<DD, R, true, CMP, 2, 2, PN>, spans[SPAN_ALL2]);
+        if (n < 500000) return group(k_nbr_group<2, R, true, CMP, 2, 4, false>, SPAN_NBR4);
+        return group(k_nbr_group<2, R, true, CMP, 2, 2, false>, SPAN_NBR2);
       }
     }
-    if (hipError_t e = group(k_nbr_group<DD, R, true, CMP, 0, DD == 3 ? 8 : 4, PN>, spans[SPAN_SMALL])) return e;
+    if (hipError_t e = group(k_nbr_group<DD, R, true, CMP, 0, DD == 3 ? 8 : 4, false>, SPAN_SMALL)) return e;
     if constexpr (DD == 3) {
-      return group(k_nbr_group<DD, R, true, CMP, 0, 4, PN>, spans[SPAN_LARGE]);
+      if (hipError_t e = group(k_nbr_group<3, R, true, CMP, 0, 4, false>, SPAN_LARGE)) return e;
+      if (hipError_t e = group(k_nbr_group<3, R, true, CMP, 0, 8, true>, SPAN_CURVED_SMALL)) return e;
+      return group(k_nbr_group<3, R, true, CMP, 0, 4, true>, SPAN_CURVED_LARGE);
     } else {
       // one lane per particle, a launch per large job
       auto one = [&](auto kern, const Span &q) {
@@ -889,15 +913,7 @@ struct sph_batch {
     using R4 = typename Vec4<R>::T;
     const Batch B = dev();
     const Parts &s = P[cur];
-    if constexpr (DD == 3) {
-      if (pair_normals) {
-        HIPCHK((launch_nbr_forces<DD, R, CMP, true>(B, s)));
-      } else {
-        HIPCHK((launch_nbr_forces<DD, R, CMP, false>(B, s)));
-      }
-    } else {
-      HIPCHK((launch_nbr_forces<DD, R, CMP, false>(B, s)));
-    }
+    HIPCHK((launch_nbr_forces<DD, R, CMP>(B, s)));
     if (DD == 3)   // 3D sweep B gathers precomputed mid-point records
       HIPCHK(launch(KID_MIDPOINT, k_midpoint<DD, R>, spans[SPAN_ALL1].blocks, BLOCK, B, s, (const R4 *)ap,
                     (R4 *)mid, spans[SPAN_ALL1].sp));
@@ -1680,7 +1696,6 @@ extern "C" sph_status sph_batch_add(sph_batch *b, const sph_geometry *g, const s
   b->n += (int)n;
   b->ncell += J.ncell;
   b->njobs = std::max(b->njobs, slot + 1);
-  b->pair_normals = b->pair_normals || (D == 3 && J.d_cpts != nullptr);
   b->invalidate_graph();
   if (sph_status st = b->update_spans()) return st;
   if (sph_status st = b->hash_range(i0, b->n)) return st;
@@ -1743,8 +1758,6 @@ extern "C" sph_status sph_batch_remove(sph_batch *b, int32_t job) {
   R.d_phi = nullptr;
   R.d_cpts = nullptr;
   R.d_coff = nullptr;
-  b->pair_normals = false;
-  for (int j : order) b->pair_normals = b->pair_normals || (b->D == 3 && b->jobs[j].d_cpts != nullptr);
   b->cur = 1 - b->cur;
   b->n = (int)off;
   b->ncell = cb;
