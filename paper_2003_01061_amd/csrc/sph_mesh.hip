@@ -18,6 +18,7 @@
 #include <cstdarg>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -596,8 +597,9 @@ struct sph_batch {
   std::vector<HostJob> jobs;
   int n = 0, njobs = 0;
   uint32_t ncell = 0;
-  char *stage = nullptr;   // pinned memory of the read-back (need_stage)
+  char *stage = nullptr;   // host memory of the read-back (need_stage)
   size_t stage_half = 0;
+  bool stage_pinned = false;
   hipEvent_t stage_ev[2] = {};
   // captured step graphs: GRAPH_LONG steps and 2 steps (both start and end at
   // buffer parity 0); long runs replay the long one, so the gap the runtime
@@ -626,7 +628,8 @@ struct sph_batch {
     for (auto e : ev_pool) (void)hipEventDestroy(e);
     for (auto e : stage_ev)
       if (e) (void)hipEventDestroy(e);
-    if (stage) (void)hipHostFree(stage);
+    if (stage_pinned) (void)hipHostFree(stage);
+    else std::free(stage);
     for (HostJob &J : jobs) {
       mem.put(J.d_grid);
       mem.put(J.d_phi);
@@ -1024,6 +1027,7 @@ struct sph_batch {
   // (pageable) memory, in two halves: one is filled while the other is
   // emptied.  48 MB take 3.7 ms that way, 4.9 ms copied straight to fresh
   // pageable memory; 60 KB 16 and 31 us.  Kept from the first read-back on.
+  // Where no memory can be pinned, ordinary memory takes its place.
   static constexpr size_t STAGE_HALF = 1u << 20;
   sph_status need_stage() {
     if (stage) return SPH_OK;
@@ -1032,19 +1036,32 @@ struct sph_batch {
                                        4095) / 4096 * 4096);
     for (hipEvent_t &e : stage_ev)
       if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    if (hipHostMalloc((void **)&stage, need > STAGE_HALF ? 2 * stage_half : stage_half, 0) != hipSuccess) {
-      stage = nullptr;
+    const size_t size = need > STAGE_HALF ? 2 * stage_half : stage_half;
+    stage_pinned = hipHostMalloc((void **)&stage, size, 0) == hipSuccess;
+    if (!stage_pinned) {
       (void)hipGetLastError();
-      return fail(SPH_ERR_OUT_OF_MEMORY, "no pinned host memory for the results");
+      stage = static_cast<char *>(std::malloc(size));
     }
-    return SPH_OK;
+    return stage ? SPH_OK : fail(SPH_ERR_OUT_OF_MEMORY, "no host memory for the results");
   }
 
   // the job's error flags and control state now
   sph_status report(int j, Report **r) {
     if (sph_status st = need_stage()) return st;
-    *r = reinterpret_cast<Report *>(stage);
-    hipLaunchKernelGGL(k_report, dim3(1), dim3(MAXF), 0, stream, dev(), j, *r);
+    Report *out = *r = reinterpret_cast<Report *>(stage);
+    if (!stage_pinned) {   // no kernel writes there: copied
+      std::vector<Group> g;
+      HIPCHK(hipMemcpyAsync(&out->st, d_st + j, sizeof(JobStat), hipMemcpyDeviceToHost, stream));
+      HIPCHK(hipMemcpyAsync(&out->gflags, d_gflags, sizeof out->gflags, hipMemcpyDeviceToHost, stream));
+      HIPCHK(pull(g, d_grp + (size_t)j * MAXF, MAXF, stream));
+      for (int f = 0; f < MAXF; ++f) {
+        out->f[f].esys = g[f].esys;
+        out->f[f].phase = g[f].phase;
+        out->f[f].tracked = g[f].tracked;
+      }
+      return SPH_OK;
+    }
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(MAXF), 0, stream, dev(), j, out);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(stream));
     return SPH_OK;
