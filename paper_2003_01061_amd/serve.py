@@ -12,11 +12,9 @@ device-resident batches and steps them with continuous batching.
   sequence of its batch; the two batches run on their own streams, so 2D and
   3D work overlaps on the device.  After every chunk of steps the server
   reads the per-job flags, retires converged jobs (positions copied to the
-  host, latency stamped) and admits what is waiting.  A job's particles cross
-  the host/device boundary only at admit and retire.  A retired job keeps its
-  slot and memory, frozen, until the next admission to its batch or until a
-  request needs them: taking it out compacts the batch and has its step graphs
-  captured again, which the admission does anyway.
+  host, latency stamped), which frees their slot and memory, and admits what
+  is waiting.  A job's particles cross the host/device boundary only at admit
+  and retire.
 * Latency.  Time from a request's arrival to its converged positions on the
   host; the report gives p50 / p99 beside the throughput.
 
@@ -64,8 +62,8 @@ class JobResult:
 
 @dataclass
 class ServeStats:
-    blocked_slots: int = 0      # admissions that found every slot taken
-    blocked_memory: int = 0     # ... no room for the particles or cells
+    blocked_slots: int = 0      # admission rounds stopped by the slot cap
+    blocked_memory: int = 0     # ... by the particle or cell capacity
     polls: int = 0
     chunks: int = 0
     max_resident: int = 0
@@ -138,7 +136,6 @@ class Server:
         results = {r.idx: JobResult(r.idx, r.dim, r.n, r.arrival) for r in reqs}
         queues = {2: deque(), 3: deque()}
         resident = {2: {}, 3: {}}
-        parked = {2: {}, 3: {}}                # retired jobs that still hold their slot and memory
         used = {d: [0, 0] for d in (2, 3)}     # particles, cells
         finished = 0
         nxt = 0
@@ -155,16 +152,6 @@ class Server:
                     from .autotune import with_cell_factor
                     spec_of[r.idx] = with_cell_factor(r.spec, cf)
             return spec_of[r.idx]
-
-        def reclaim(d):
-            for job, rj in parked[d].items():
-                self.batches[d].remove(job)
-                used[d][0] -= rj.req.n
-                used[d][1] -= rj.cells
-            parked[d].clear()
-
-        def slots_taken():
-            return sum(len(resident[d]) + len(parked[d]) for d in (2, 3))
         t0 = self.clock()
         st = self.stats
         st.max_particles = {2: 0, 3: 0}
@@ -192,13 +179,9 @@ class Server:
                         res.message = "larger than the batch capacity" if cells >= 0 else "invalid job"
                         finished += 1
                         continue
-                    if slots_taken() >= self.slots:
+                    if sum(len(x) for x in resident.values()) >= self.slots:
                         st.blocked_slots += 1
-                        for dd in (2, 3):
-                            reclaim(dd)
-                        if slots_taken() >= self.slots:
-                            break
-                    reclaim(d)
+                        break
                     if (used[d][0] + r.n > self.cap_particles[d]
                             or used[d][1] + cells > self.cap_cells[d]):
                         st.blocked_memory += 1
@@ -248,17 +231,12 @@ class Server:
                             res.positions = x
                     except Exception as e:
                         res.status, res.message, res.done = "error", str(e), now()
-                    if res.status == "ok":
-                        parked[d][job] = rj
-                    else:                        # still moving, or unusable: out at once
-                        b.remove(job)
-                        used[d][0] -= rj.req.n
-                        used[d][1] -= rj.cells
+                    b.remove(job)
+                    used[d][0] -= rj.req.n
+                    used[d][1] -= rj.cells
                     finished += 1
                     if progress:
                         progress(res)
-        for d in (2, 3):
-            reclaim(d)
         return [results[r.idx] for r in sorted(reqs, key=lambda r: r.idx)]
 
 
