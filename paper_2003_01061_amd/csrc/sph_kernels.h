@@ -1923,6 +1923,10 @@ __global__ __launch_bounds__(BLOCK) void k_midpoint(Batch B, Parts s,
 // Lane l of the particle's G takes the entries l, l + G, ..., NB of them at a
 // time; boundary entries and places past the list take the particle itself,
 // with no weight.  The caller adds the lanes' sums.
+// A lane alone reads half a block of its list at a time, and in FP32 leaves the
+// loop and skips boundary entries by itself, which gathers less (1,000,000
+// particles in 2D: 53.5 us, all lanes together 56); the FP64 sums lose by that
+// (96.8 against 94).
 template <int D, int K, typename R, bool MID, bool CMP, int G>
 __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4<R>::T *__restrict__ ap,
                                              const typename Vec4<R>::T *__restrict__ mid,
@@ -1945,12 +1949,26 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
 #pragma unroll
   for (int a = 0; a < 3; ++a) aF[a].init(0.0);
   constexpr int NB = 4;
-  for (uint32_t e0 = 0; any_lane(e0 < cnt); e0 += NB * G) {
+  static_assert(LB % NB == 0, "half a block at a time");
+  constexpr bool ALONE = G == 1 && sizeof(R) == 4;
+  for (uint32_t e0 = 0; ALONE ? e0 < cnt : any_lane(e0 < cnt); e0 += NB * G) {
     uint32_t u[NB];
+    if constexpr (G == 1) {
+      uint4 w = make_uint4(0u, 0u, 0u, 0u);
+      if (e0 < cnt)
+        w = reinterpret_cast<const uint4 *>(nbr)[((size_t)(e0 / LB) * n + i) * (LB / 4) + e0 % LB / 4];
+      u[0] = w.x;
+      u[1] = w.y;
+      u[2] = w.z;
+      u[3] = w.w;
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      const uint32_t e = e0 + q * G + lane;
-      u[q] = e < cnt ? nbr[((size_t)(e / LB) * n + i) * LB + e % LB] : 0x80000000u;
+      for (int q = 0; q < NB; ++q) u[q] = e0 + q < cnt ? u[q] : 0x80000000u;
+    } else {
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        const uint32_t e = e0 + q * G + lane;
+        u[q] = e < cnt ? nbr[((size_t)(e / LB) * n + i) * LB + e % LB] : 0x80000000u;
+      }
     }
     double4 xr[NB];
     float4 fr[NB];
@@ -1967,6 +1985,7 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
       // look each time; the FP32 ones, bound by the gathers, gain more from
       // entries that overlap (2,000,000 particles in 3D 290 us, looking 333).
       if (sizeof(R) == 8 && q > 0 && !any_lane(e0 + q * G + lane < cnt)) break;
+      if (ALONE && u[q] >> 31) continue;
       R dx0, dx1, dx2, hj;
       if constexpr (XF) {
         dx0 = (R)(xfi.x - fr[q].x);
@@ -2017,11 +2036,11 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
 // neighbouring entries, which share cache lines.  Bound by the two gathers per
 // neighbour in FP32, by the arithmetic in FP64 and, for a few thousand
 // particles, by the chain of loads.  us before (one lane in 2D, two in 3D) and
-// now: 4,352 particles in 2D, FP64, 13.6 / 7.8; 2,503, FP32, 11.3 / 7.7;
-// 1,000,000 62 / 59; 3D 30,000, FP64, 20.6 / 16; 66,000, FP32, calibrated, 25
-// / 20; 300,000 between ellipsoids 65 / 52; 2,000,000 295 / 267.  The gathers
-// want waves: of 2,000,000 particles 296 us with 86 registers (5 waves a SIMD),
-// 267 with 80 (6), 420 with 72, which spill.
+// now: 4,352 particles in 2D, FP64, 13.6 / 7.8; 2,503, FP32, 11.3 / 7.7; 3D
+// 30,000, FP64, 20.6 / 16; 66,000, FP32, calibrated, 25 / 20; 300,000 between
+// ellipsoids 65 / 52; 2,000,000 295 / 267.  Large 2D jobs keep one lane
+// (small_job).  The gathers want waves: of 2,000,000 particles in 3D 296 us with
+// 86 registers (5 waves a SIMD), 267 with 80 (6), 420 with 72, which spill.
 // ---------------------------------------------------------------------------
 template <int D, typename R, bool CMP, int G>
 __global__ __launch_bounds__(BLOCK, sizeof(R) == 4 ? 6 : 4) void k_sweep_b(Batch B, Parts s,
@@ -2095,7 +2114,7 @@ __global__ __launch_bounds__(BLOCK, sizeof(R) == 4 ? 6 : 4) void k_sweep_b(Batch
     xp = s.xh[p];
     vp = s.v[p];
   }
-  __syncthreads();
+  if (G > 1) __syncthreads();   // a lane alone reads what it wrote
   if ((int)threadIdx.x >= (PB < 64 ? 64 : PB)) return;
   bool act = false;
   unsigned long long dtb = ~0ull;

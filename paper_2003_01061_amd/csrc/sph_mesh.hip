@@ -764,7 +764,7 @@ struct sph_batch {
            : k == SPAN_ALL1                                        ? 1
            : k == SPAN_NBR2                                        ? 2
            : k == SPAN_SMALL || k == SPAN_CURVED_SMALL             ? (D == 3 ? 8 : 4)
-                                                                   : (D == 3 ? 4 : 2);
+                                                                   : (D == 3 ? 4 : 1);
   }
   bool in_span(int k, const HostJob &J) const {
     if (k <= SPAN_ALL1) return true;
@@ -785,11 +785,20 @@ struct sph_batch {
   // lists' last places.  Cell scan and sums, FP32, us per launch.  3D, 8 against
   // 4 lanes: 30,000 particles 36 / 49, 200,000 128 / 125, 400,000 229 / 215,
   // 800,000 447 / 408; with a reach of 2.5h, whose lists do not fit 4 lanes'
-  // LDS, 400,000 368 / 427.  2D, 4 lanes against one: 20,000 14 / 28, 100,000
-  // 25 / 30, 200,000 38 / 36, 300,000 51 / 54, 450,000 72 / 65.
+  // LDS, 400,000 368 / 427.  2D, 4 lanes against one, FP32 and FP64: 50,000
+  // 17.7 / 25.6 and 18.6 / 28.1, 100,000 23.5 / 27.2 and 26.0 / 31.5, 150,000
+  // 29.5 / 31.4 and 33.2 / 36.8, 200,000 35.8 / 32.9 and 40.3 / 39.4, 250,000 42.2
+  // / 33.8 and 47.5 / 41.4, 300,000 49.1 / 50.1 and 55.6 / 57.7, 400,000 61.0 / 56.7
+  // and 68.9 / 67.1, 1,000,000 148 / 117 and 166 / 143.  (Of the one-lane blocks
+  // 1,024 run at once: 262,144 particles fill the chip, a few more begin a
+  // second round.)  Sweep B in 2D, the same: 50,000 9.5 / 11.1 and 12.4 / 15.2,
+  // 100,000 12.4 / 13.0 and 18.6 / 19.8, 150,000 15.8 / 15.6 and 24.9 / 25.2,
+  // 200,000 19.2 / 16.9 and 31.1 / 29.2, 250,000 22.8 / 17.8 and 37.6 / 31.4,
+  // 1,000,000 71.9 / 53.5 and 134 / 94; 2 lanes 18.0, 20.1, 59 and 28.5, 32.4, 106
+  // at the last three sizes.
   static bool long_lists(const HostJob &J) { return J.dev.ksup > 2.25; }
   bool small_job(const HostJob &J) const {
-    return D == 3 ? J.n < 200000 || long_lists(J) : J.n < 300000;
+    return D == 3 ? J.n < 200000 || long_lists(J) : J.n < 175000;
   }
 
   // tables of the resident jobs; call when they or their slots have changed
@@ -922,8 +931,8 @@ struct sph_batch {
                     (R4 *)mid, spans[SPAN_ALL1].sp));
     // Sweep B.  3D takes 4 lanes a particle: 8 are slower from 30,000 particles
     // on (2,000,000: 404 against 290 us), 2 below (66,000: 28 against 20).  2D
-    // takes 4 for small jobs (2,503 particles: 7.2 us, 2 lanes 9.6) and 2 for
-    // large ones (1,000,000: 59 us, 4 lanes 63; equal at 250,000).
+    // takes 4 for small jobs (2,503 particles: 7.2 us, 2 lanes 9.6) and one for
+    // large ones (small_job has both).
     auto sweep_b = [&](auto kern, const SpanSet &S) {
       return launch(KID_SWEEP_B, kern, S.blocks, BLOCK, B, s, (const uint32_t *)nbr, (const uint32_t *)nnb,
                     (const R4 *)ap, (const R4 *)mid, (R4 *)acc, dbg_vm, S.sp);
@@ -932,7 +941,7 @@ struct sph_batch {
       HIPCHK(sweep_b(k_sweep_b<DD, R, CMP, 4>, spans[SPAN_ALL4]));
     } else {
       HIPCHK(sweep_b(k_sweep_b<DD, R, CMP, 4>, spans[SPAN_SMALL]));
-      HIPCHK(sweep_b(k_sweep_b<DD, R, CMP, 2>, spans[SPAN_LARGE]));
+      HIPCHK(sweep_b(k_sweep_b<DD, R, CMP, 1>, spans[SPAN_LARGE]));
     }
     HIPCHK(launch(KID_INTEGRATE_HASH, k_integrate_hash<DD, R>, spans[SPAN_ALL1].blocks, BLOCK, B, s,
                   (const R4 *)acc, cell, rank, cnt, spans[SPAN_ALL1].sp));
