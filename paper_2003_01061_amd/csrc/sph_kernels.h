@@ -1098,11 +1098,11 @@ __global__ __launch_bounds__(BLOCK) void k_nbr_forces(
 // A position of u cells along an axis as whole cells and a fraction.  A
 // particle the caller put 2^30 cells or farther off the grid (of at most 2^29
 // cells) is taken to be that far off: its ranges end in the same border cells,
-// and a whole part plus a half chord stays an int.  A NaN stays one.
+// and a whole part plus a half chord stays an int.  So is a NaN, which has no
+// neighbours.
 __host__ __device__ __forceinline__ void cell_split(double u, int &whole, float &frac) {
   constexpr double FAR = 1073741824.0;
-  u = u > FAR ? FAR : u;
-  u = u < -FAR ? -FAR : u;
+  u = __builtin_fmax(__builtin_fmin(u, FAR), -FAR);
   const double f = __builtin_floor(u);
   whole = (int)f;
   frac = (float)(u - f);
