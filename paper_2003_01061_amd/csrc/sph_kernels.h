@@ -456,8 +456,12 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(int n, const uint32_t *__rest
 // particle keeps its slot, clears its cell's count and refreshes its boundary
 // normal; at a rebuild the sorted copy goes to b (whose slot also records x
 // and h), and the list build copies it back into a.
+// Bound by memory and its latency.  The bound on the registers keeps the
+// closest-point search, which only curve particles run, from costing the others
+// their waves: of 2,000,000 particles in 3D 83.1 us with 73 registers (6 waves a
+// SIMD), 76.0 with 58 (8).
 template <int D>
-__global__ __launch_bounds__(BLOCK) void k_rank_gather(Batch B, int n, const uint32_t *__restrict__ psrc,
+__global__ __launch_bounds__(BLOCK, 8) void k_rank_gather(Batch B, int n, const uint32_t *__restrict__ psrc,
                                                        const uint32_t *__restrict__ pkey,
                                                        const uint32_t *__restrict__ cell,
                                                        const uint32_t *__restrict__ cstart,
