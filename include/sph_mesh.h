@@ -195,9 +195,14 @@ typedef struct {
   double cell_factor;        /* cell side = r_c,min cell_factor, r_c,min the
                                 support radius kernel_support h_min (0 = 1.0), enlarged
                                 if the grid would exceed 2^29 cells */
-  int32_t scan_tile;         /* candidate records tested per pass of the
-                                neighbour scan: 2, 4 or 8; 0 = 4.  Results do
-                                not depend on it (autotuning knob) */
+  int32_t scan_tile;         /* candidate records tested per pass of the scan
+                                with one lane per particle: 2, 4 or 8; 0 = 4.
+                                That scan serves 2D jobs of 175,000 particles
+                                or more without Verlet lists and 2D list
+                                builds of 200,000 or more; other work takes
+                                several lanes per particle and ignores the
+                                tile.  Results do not depend on it
+                                (autotuning knob) */
   int32_t cell_levels;       /* cell grids per band of h: level l holds the
                                 particles with h_min 2^l <= h < h_min 2^(l+1)
                                 on cells of side kernel_support h_min 2^l

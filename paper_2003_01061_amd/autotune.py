@@ -7,8 +7,9 @@ The knobs are the ones that change speed but not the method:
   predicate, but every particle visits more cell rows.  Changing it changes
   the canonical (cell, caller id) order of a neighbour list, hence the
   rounding of the force sums, never the list itself.
-* ``scan_tile`` -- candidate records the neighbour scan loads and tests per
-  pass (2, 4 or 8; per batch).  Results are bit-identical for every value.
+* ``scan_tile`` -- candidate records the scan with one lane per particle loads
+  and tests per pass (2, 4 or 8; per batch).  Results are bit-identical for
+  every value.  Only large 2D work takes that scan (``tile_matters``).
 * ``verlet_skin`` -- reach of the Verlet candidate lists beyond the cut-off
   radius, in units of h (0: a cell scan and a sort every step).  A wider skin
   means fewer rebuilds but more candidates to filter every step.  The lists
@@ -21,7 +22,8 @@ list format is ELL, so neither is searched.
 ``tune`` times every (cell_factor, scan_tile) configuration of the grid on a
 trial batch holding the given jobs (the graph-replayed step, after warm-up
 steps), then every (skin, scan_tile) pair at the fastest cell factor, and
-returns the fastest; ties keep the earlier (default-first) entry, and a
+returns the fastest.  Where no kernel reads the tile, its values are the same
+configuration and are timed once; ties keep the earlier (default-first) entry, and a
 configuration replaces the default (or, at a skin, the best pair's tile) only
 when it is faster by more than a noise margin.  The timing sources are injectable so
 that the selection logic is testable without a GPU.
@@ -37,6 +39,18 @@ DEFAULT = {"cell_factor": 1.0, "scan_tile": 4, "verlet_skin": 0.0}
 CELL_FACTORS = (1.0, 0.75, 1.25)
 SCAN_TILES = (4, 2, 8)
 SKINS = (0.3, 0.5, 0.8)
+# particles from which a 2D job without Verlet lists, and the list build of a 2D
+# batch, take one lane per particle (ONE_LANE and ONE_LANE_BUILD of sph_mesh.hip)
+ONE_LANE, ONE_LANE_BUILD = 175_000, 200_000
+
+
+def tile_matters(specs, dim, skin):
+    """Does a kernel of these jobs' step read the scan tile?"""
+    if dim != 2:
+        return False
+    if skin > 0.0:
+        return sum(s.n for s in specs) >= ONE_LANE_BUILD
+    return any(s.n >= ONE_LANE for s in specs)
 
 
 @dataclass
@@ -100,12 +114,18 @@ def tune(specs: Sequence, dim: int, precision: int, cell_factors=CELL_FACTORS,
     if not specs:
         raise ValueError("tune needs at least one job")
     if measure is None:
+        timed = {}
+
+        def once(cf, tile, skin):
+            key = (cf, tile if tile_matters(specs, dim, skin) else None, skin)
+            if key not in timed:
+                timed[key] = _time_config(specs, dim, precision, cf, tile, steps, warmup, max_neighbors, skin)
+            return timed[key]
+
         def measure(cf, tile):
-            return _time_config(specs, dim, precision, cf, tile, steps, warmup, max_neighbors)
+            return once(cf, tile, 0.0)
         if measure_skin is None:
-            def measure_skin(cf, tile, skin):
-                return _time_config(specs, dim, precision, cf, tile, steps, warmup,
-                                    max_neighbors, skin)
+            measure_skin = once
     grid = [(cf, t) for cf in cell_factors for t in scan_tiles]
     if (DEFAULT["cell_factor"], DEFAULT["scan_tile"]) not in grid:
         grid.insert(0, (DEFAULT["cell_factor"], DEFAULT["scan_tile"]))

@@ -796,9 +796,10 @@ struct sph_batch {
   // 200,000 19.2 / 16.9 and 31.1 / 29.2, 250,000 22.8 / 17.8 and 37.6 / 31.4,
   // 1,000,000 71.9 / 53.5 and 134 / 94; 2 lanes 18.0, 20.1, 59 and 28.5, 32.4, 106
   // at the last three sizes.
+  static constexpr int ONE_LANE = 175000;
   static bool long_lists(const HostJob &J) { return J.dev.ksup > 2.25; }
   bool small_job(const HostJob &J) const {
-    return D == 3 ? J.n < 200000 || long_lists(J) : J.n < 175000;
+    return D == 3 ? J.n < 200000 || long_lists(J) : J.n < ONE_LANE;
   }
 
   // tables of the resident jobs; call when they or their slots have changed
@@ -849,6 +850,7 @@ struct sph_batch {
   // 3D, skin 0.5h, 8 against 4 lanes: 30,000 particles 9.8 / 14.2, 200,000 24 /
   // 28, 400,000 42 / 46, 800,000 82 / 83; 2D, skin 0.8h, 4 lanes against one: 20,000 4.9 / 6.5,
   // 100,000 6.4 / 6.8, 250,000 9.1 / 8.3, 500,000 14.5 / 12.8.
+  static constexpr int ONE_LANE_BUILD = 200000;
   template <int DD>
   hipError_t launch_build(const Batch &B, const Parts &s) {
     const Parts &t = P[1 - cur];
@@ -860,7 +862,7 @@ struct sph_batch {
       if (n < 800000) return group(k_nbr_group<3, float, false, false, 1, 8, false>, spans[SPAN_ALL8]);
       return group(k_nbr_group<3, float, false, false, 1, 4, false>, spans[SPAN_ALL4]);
     } else {
-      if (n < 200000) return group(k_nbr_group<2, float, false, false, 1, 4, false>, spans[SPAN_ALL4]);
+      if (n < ONE_LANE_BUILD) return group(k_nbr_group<2, float, false, false, 1, 4, false>, spans[SPAN_ALL4]);
       auto one = [&](auto kern) {
         return launch(KID_SKIN, kern, blocks8(n), BLOCK, B, t, (const uint32_t *)cstart, 0, nbr, nnb,
                       (float4 *)nullptr, (double *)nullptr, (double *)nullptr, s, 0, n);
