@@ -552,636 +552,30 @@ __global__ __launch_bounds__(BLOCK, 8) void k_rank_gather(Batch B, int n, const 
   }
 }
 
+// does v hold in a lane of the wave (on the host: a lane by itself)
+__host__ __device__ __forceinline__ bool any_lane(bool v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_ballot_w64(v) != 0ull;
+#else
+  return v;
+#endif
+}
+#ifdef __HIP_DEVICE_COMPILE__
+using LdsList = const __attribute__((address_space(3))) uint32_t *;
+#else
+using LdsList = const uint32_t *;
+#endif
+
 // ---------------------------------------------------------------------------
 // Pair sums of sweep A (Eqs. (gamma_disc_renormSPH), (particle_volume),
 // (sph_pressure_force_disc_weighted)) of particle i of intrinsic dimension K
-// over its neighbour list.  Pair terms are evaluated in R and accumulated by
-// Sum<CMP>: in FP64, or (CMP, R = float) in FP32 with Neumaier compensation.
+// over its neighbour list, by G lanes: lane l takes the entries l, l + G, ...,
+// NB of them at a time, and the caller adds the lanes' sums.  Pair terms are
+// evaluated in R and accumulated by Sum<CMP>: in FP64, or (CMP, R = float) in
+// FP32 with Neumaier compensation.
 // ---------------------------------------------------------------------------
-template <int D, int K, typename R, bool CMP>
-__host__ __device__ __forceinline__ void sweep_a_sums(const Geom &g, const Parts &s,
-                                             const double4 *__restrict__ enrm,
-                                             const BNorm *__restrict__ bnrow, int bw, double p0,
-                                             double klen, double bscale,
-                                             const uint32_t *__restrict__ nbr, int n, int i,
-                                             uint32_t cnt, const double4 &xi, int fi, bool pair_normals,
-                                             double &S, double &gam, double Pi[3], double B[3],
-                                             const uint32_t *ring = nullptr, uint32_t ring_len = 0,
-                                             uint32_t ring_stride = 0, uint32_t lane = 0,
-                                             uint32_t nlanes = 1) {
-  // h enters rho_t = h^-k; the kernel is evaluated at the smoothing length
-  // klen h (cut-off radius 2 klen h)
-  const R hi = (R)xi.w;
-  const R kl = (R)klen;
-  const R ihi = rcp_((R)(klen * xi.w));
-  constexpr R alpha = kalphaK<K, R>();
-  const R hik = powK<K>(hi), hi2k = hik * hik;
-  const R ihik = powK<K>(ihi);
-  const R P0 = (R)p0;
-  const R wself = alpha * ihik;
-  // with several lanes per particle, lane l sums the batches l, l + nlanes,
-  // ... of the list (the self term in lane 0); the caller adds the lanes' sums
-  Sum<CMP> aS, aG, aP[3], aB[3];
-  aS.init(lane == 0 ? (double)wself : 0.0);
-  aG.init(lane == 0 ? (double)(wself * hik) : 0.0);
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    aP[a].init(0.0);
-    aB[a].init(0.0);
-  }
-  constexpr int NB = SPH_NBATCH;
-  static_assert(NB == 4 || NB == LB, "record batches of 4 or 8 tile a list block");
-  // records gathered together: GB of a batch's NB (fewer live registers)
-  constexpr int GB = SPH_GBATCH < NB ? SPH_GBATCH : NB;
-  static_assert(NB % GB == 0, "gather groups tile a batch");
-  // The list's last entries may also sit in the caller's LDS ring (entry e
-  // in slot e % ring_len, column stride ring_stride): entries from lbase on
-  // are read there, the ones before from the list in memory (whole blocks,
-  // as lbase is a multiple of LB).  Either way every entry is read in list
-  // order, so the sums are the same.
-  uint32_t lbase = cnt;
-  if (ring != nullptr) lbase = cnt > ring_len ? (cnt - ring_len + LB - 1) / LB * LB : 0u;
-  const uint4 *gl = reinterpret_cast<const uint4 *>(nbr) + (size_t)i * (LB / 4);
-  for (uint32_t e0 = NB * lane; e0 < cnt; e0 += NB * nlanes) {
-    {
-      uint32_t u[NB];
-      if (e0 < lbase) {   // NB entries of a block in memory: 16-byte loads
-#pragma unroll
-        for (int h = 0; h < NB / 4; ++h) {
-          const uint4 w = gl[(size_t)(e0 / LB) * n * (LB / 4) + (e0 % LB) / 4 + h];
-          u[4 * h] = w.x;
-          u[4 * h + 1] = w.y;
-          u[4 * h + 2] = w.z;
-          u[4 * h + 3] = w.w;
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < NB; ++q) u[q] = ring[((e0 + q) % ring_len) * ring_stride];
-      }
-#pragma unroll
-      for (int q = 0; q < NB; ++q) u[q] = e0 + q < cnt ? u[q] : 0u;
-#pragma unroll
-      for (int g0 = 0; g0 < NB; g0 += GB) {
-      double4 xr[GB];
-#pragma unroll
-      for (int q = 0; q < GB; ++q) xr[q] = s.xh[u[g0 + q] & 0x7fffffffu];
-#pragma unroll
-      for (int qg = 0; qg < GB; ++qg) {
-        const int q = g0 + qg;
-        if (e0 + q >= cnt) break;
-        const double4 xj = xr[qg];
-        const R dx0 = (R)(xi.x - xj.x), dx1 = (R)(xi.y - xj.y);
-        const R dx2 = D == 3 ? (R)(xi.z - xj.z) : R(0);
-        const R rr = sqrt_(dx0 * dx0 + dx1 * dx1 + dx2 * dx2);
-        const R hj = (R)xj.w;
-        const R hjk = powK<K>(hj);
-        const R hsum = hi2k + hjk * hjk;
-        const R ihij = rcp_(kl * (R(0.5) * (hi + hj)));
-        const R qij = rr * ihij;
-        if (!(u[q] >> 31)) {
-          const R w = alpha * wshapeK<K>(rr * ihi) * ihik;           // W(r, h_i)
-          aS.add(w);
-          aG.add(w * hjk);
-          const R ih2 = ihij * ihij;
-          const R ihk2 = K == 1 ? ih2 * ihij : (K == 2 ? ih2 * ih2 : ih2 * ih2 * ihij);
-          const R c = P0 * hsum * alpha * dwqK<K>(qij) * ihk2;       // (dW/dr)/r at h_ij
-          aP[0].add(c * dx0);
-          aP[1].add(c * dx1);
-          if (D == 3) aP[2].add(c * dx2);
-        } else {
-          // the particle volume (Eq. (particle_volume)) is the inverse of i's
-          // number density: the boundary particles that act on i count too
-          aS.add(alpha * wshapeK<K>(rr * ihi) * ihik);
-          double nv[3];
-          if constexpr (K == D) {   // the volume: the domain's normal k_rank_gather stored at b
-            const double4 e = enrm[u[q] & 0x7fffffffu];
-            nv[0] = e.x;
-            nv[1] = e.y;
-            nv[2] = e.z;
-          } else {
-            const int fj = s.f[u[q] & 0x7fffffffu];
-            const BNorm N = bnrow[fj & (MAXF - 1)];
-            if (D == 3 && N.mode >= 7) continue;   // normal of the pair: the pass below
-            if (N.mode >= 2) {   // a curved boundary: the normal k_rank_gather stored
-              const double4 e = enrm[u[q] & 0x7fffffffu];
-              nv[0] = e.x;
-              nv[1] = e.y;
-              nv[2] = e.z;
-            } else {
-              nv[0] = N.n[0];
-              nv[1] = N.n[1];
-              nv[2] = N.n[2];
-            }
-          }
-          const R om = (bw == 0 ? rcp_(hj) : (bw == 1 ? powK<K>(hj) * rcp_(hj) : R(0))) * (R)bscale;
-          const R w = alpha * wshapeK<K>(qij) * powK<K>(ihij);          // W(r, h_ib)
-          if constexpr (CMP) {   // FP32 terms: the normal rounded to FP32
-            const float c = (float)(P0 * hsum * w * om);
-            aB[0].add(c * (float)nv[0]);
-            aB[1].add(c * (float)nv[1]);
-            if (D == 3) aB[2].add(c * (float)nv[2]);
-          } else {
-            const double c = (double)(P0 * hsum * w * om);
-            aB[0].add(c * nv[0]);
-            aB[1].add(c * nv[1]);
-            if (D == 3) aB[2].add(c * nv[2]);
-          }
-        }
-      }
-      }
-    }
-  }
-  if constexpr (D == 3) {
-    // A 3D surface patch at a curve (mode 7) or vertex (8) beside it: the
-    // normal is the direction to b within i's tangent plane (i's stored
-    // normal removed), at a curve also without the part along b's closest
-    // segment, normalised.  Only patch particles of a geometry with imported
-    // curves take this pass, which keeps its registers out of the main loop.
-    if (pair_normals) {
-      const double4 ei = enrm[i];
-      for (uint32_t e = lane; e < cnt; e += nlanes) {
-        const uint32_t v = nbr[((size_t)(e / LB) * n + i) * LB + e % LB];
-        if (!(v >> 31)) continue;
-        const uint32_t b = v & 0x7fffffffu;
-        const BNorm N = bnrow[s.f[b] & (MAXF - 1)];
-        if (N.mode < 7) continue;
-        const double4 xj = s.xh[b];
-        const R dx0 = (R)(xi.x - xj.x), dx1 = (R)(xi.y - xj.y), dx2 = (R)(xi.z - xj.z);
-        const R rr = sqrt_(dx0 * dx0 + dx1 * dx1 + dx2 * dx2);
-        double d0 = xj.x - xi.x, d1 = xj.y - xi.y, d2 = xj.z - xi.z;
-        const double dm = d0 * ei.x + d1 * ei.y + d2 * ei.z;
-        d0 -= dm * ei.x;
-        d1 -= dm * ei.y;
-        d2 -= dm * ei.z;
-        if (N.mode == 7) {
-          double t[3];
-          seg_tangent<3>(g, (int)enrm[b].w, t);
-          const double dt = d0 * t[0] + d1 * t[1] + d2 * t[2];
-          d0 -= dt * t[0];
-          d1 -= dt * t[1];
-          d2 -= dt * t[2];
-        }
-        const double l = __builtin_sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-        const double il = l > 0.0 ? 1.0 / l : 0.0;
-        const double nv[3] = {d0 * il, d1 * il, d2 * il};
-        const R hj = (R)xj.w;
-        const R hjk = powK<K>(hj);
-        const R hsum = hi2k + hjk * hjk;
-        const R ihij = rcp_(kl * (R(0.5) * (hi + hj)));
-        const R om = (bw == 0 ? rcp_(hj) : (bw == 1 ? powK<K>(hj) * rcp_(hj) : R(0))) * (R)bscale;
-        const R w = alpha * wshapeK<K>(rr * ihij) * powK<K>(ihij);      // W(r, h_ib)
-        if constexpr (CMP) {
-          const float c = (float)(P0 * hsum * w * om);
-          aB[0].add(c * (float)nv[0]);
-          aB[1].add(c * (float)nv[1]);
-          aB[2].add(c * (float)nv[2]);
-        } else {
-          const double c = (double)(P0 * hsum * w * om);
-          aB[0].add(c * nv[0]);
-          aB[1].add(c * nv[1]);
-          aB[2].add(c * nv[2]);
-        }
-      }
-    }
-  }
-  S = aS.get();
-  gam = aG.get();
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    Pi[a] = aP[a].get();
-    B[a] = aB[a].get();
-  }
-}
-
-// Appends the hits among tag[0, NB) (0xffffffff: no hit) to a particle's
-// column of the LDS ring (slot k at rc[k * stride], slot = entry mod LR) and
-// stores each list block they complete to *wp as two 16-byte writes, while
-// the capacity of nblk blocks allows.  With a ring of two blocks or more the
-// block a batch completes is still whole after the batch (NB <= LB hits
-// reach at most LB - 1 entries into the next block), so the test for a
-// store runs once per batch instead of once per hit.
-template <int NB, int LR>
-__host__ __device__ __forceinline__ void append_hits(const uint32_t (&tag)[NB], uint32_t *rc,
-                                                     int stride, uint32_t &count, uint4 *&wp,
-                                                     uint32_t wstep, uint32_t nblk) {
-  static_assert(NB <= LB && LR % LB == 0, "a batch completes at most one block");
-  if constexpr (LR >= 2 * LB) {
-    const uint32_t c0 = count;
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      if (tag[q] != 0xffffffffu) {
-        rc[(count % LR) * stride] = tag[q];
-        ++count;
-      }
-    }
-    if (count / LB != c0 / LB && count / LB <= nblk) {
-      const uint32_t k0 = (c0 / LB * LB) % LR;
-      wp[0] = make_uint4(rc[k0 * stride], rc[(k0 + 1) * stride], rc[(k0 + 2) * stride],
-                         rc[(k0 + 3) * stride]);
-      wp[1] = make_uint4(rc[(k0 + 4) * stride], rc[(k0 + 5) * stride], rc[(k0 + 6) * stride],
-                         rc[(k0 + 7) * stride]);
-      wp += wstep;
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      if (tag[q] != 0xffffffffu) {
-        const uint32_t k = count % LR;
-        rc[k * stride] = tag[q];
-        ++count;
-        if (k % LB == LB - 1 && count / LB <= nblk) {
-          const uint32_t k0 = k - (LB - 1);
-          wp[0] = make_uint4(rc[k0 * stride], rc[(k0 + 1) * stride], rc[(k0 + 2) * stride],
-                             rc[(k0 + 3) * stride]);
-          wp[1] = make_uint4(rc[(k0 + 4) * stride], rc[(k0 + 5) * stride], rc[(k0 + 6) * stride],
-                             rc[(k0 + 7) * stride]);
-          wp += wstep;
-        }
-      }
-    }
-  }
-}
-
-// the classification's band (JobDev) of a particle that lies outside its job's
-// box, where the caller may have put it
-template <int D, int MODE>
-__device__ __forceinline__ void band_beyond(const JobDev &J, const double4 &xi, float &cin, float &cout) {
-  double xb = __builtin_fabs(xi.x);
-  xb = __builtin_fabs(xi.y) > xb ? __builtin_fabs(xi.y) : xb;
-  if (D == 3) xb = __builtin_fabs(xi.z) > xb ? __builtin_fabs(xi.z) : xb;
-  xb += 2.0 * J.rmax_s + 2.0 * J.G.cmax;
-  const double w = (D == 2 ? 2e-6 : 2e-5) +
-                   (D == 3 ? 1.7320508075688772 : 1.4142135623730951) * 0x1p-23 * xb * 1.01 * J.iband;
-  const double k = MODE == 1 ? 0.5 * J.ksup_s : J.klen;
-  cin = w < 1.0 ? (float)((1.0 - w) * (1.0 - w) * k * k) : -1.0f;
-  cout = (float)((1.0 + w) * (1.0 + w) * k * k);
-}
-
-// ---------------------------------------------------------------------------
-// neighbour list (Algorithm 1 "construct Verlet neighbor list") and, in the
-// same launch, sweep A over it; FORCES = false builds lists only.  Two kernels
-// make the same lists: k_nbr_forces, one lane per particle, and k_nbr_group, G
-// lanes per particle.  The candidate scan covers, for every cell row within
-// R_i of x_i, only the cells under the chord of the disc (sphere) of radius
-// R_i, so no neighbour is skipped and fewer non-neighbours are tested.  The pair
-// sums then run over the list just written, so the force math executes once
-// per neighbour instead of once per candidate.  Every particle reads its own
-// job's geometry and grid; cells of different jobs never meet.
-//
-// k_nbr_forces: one lane per particle of the slots [i0, i1).  It is the faster
-// for large 2D jobs (launch_nbr_forces), whose short lists do not fill several
-// lanes: of 1,000,000 particles, FP32, cell scan, 119 us against 135 with 2
-// lanes and 157 with 4; the list build 170 against 225 us.
-// MODE 0: candidates from the cell scan, as above.  MODE 1 (FORCES = false,
-// only when a rebuild is due): the Verlet candidate list of every
-// non-singular particle, the cell scan at the reach (c + delta) h with the
-// FP32 test alone, widened by its error bound so that it keeps every pair
-// within that reach.
-// ---------------------------------------------------------------------------
-template <int D, typename R, bool FORCES, int NB, bool CMP, int MODE>
-__global__ __launch_bounds__(BLOCK) void k_nbr_forces(
-    Batch B, Parts s, const uint32_t *__restrict__ cstart, int all, uint32_t *__restrict__ nbr,
-    uint32_t *__restrict__ nnb, typename Vec4<R>::T *__restrict__ ap,
-    double *__restrict__ dbg_gam, double *__restrict__ dbg_vt, Parts home, int i0, int i1) {
-  static_assert(MODE == 0 || (MODE == 1 && !FORCES), "candidate list modes");
-  if (MODE == 1) {
-    if (B.vstate[VS_REBUILD] == 0ull) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) B.vstate[VS_BUILDS] += 1ull;
-    // s holds the particles just sorted; they go back to the buffer the
-    // steps use between rebuilds (no kernel of this launch reads it)
-    const int c = i0 + xcd_block() * BLOCK + (int)threadIdx.x;
-    if (c < i1) {
-      home.xh[c] = s.xh[c];
-      home.v[c] = s.v[c];
-      home.f[c] = s.f[c];
-      home.oid[c] = s.oid[c];
-      home.xf[c] = s.xf[c];
-    }
-  }
-  using R4 = typename Vec4<R>::T;
-  // hits collect in the thread's own column of an LDS ring of LR entries (a
-  // multiple of LB; see the append below); it keeps the last LR entries, so
-  // that in the FP32 modes a list no longer than LR stays whole in LDS,
-  // where the pair sums read it (the FP64 sums read the list from memory:
-  // the ring's addressing would cost them a wave per SIMD); the Verlet build
-  // keeps two blocks, so that its block stores are tested once per batch
-  constexpr bool LDS_SUMS = FORCES && sizeof(R) == 4;
-  constexpr int LR = LDS_SUMS ? SPH_LDS_LIST : (MODE == 1 ? 2 * LB : LB);
-  static_assert(LR % LB == 0, "the ring holds whole blocks");
-  __shared__ uint32_t ring[LR][BLOCK];
-  const int col = (int)threadIdx.x;
-  const int n = B.n;
-  const int i = i0 + xcd_block() * BLOCK + (int)threadIdx.x;
-  bool act = false;
-  int fi = 0, job = 0;
-  unsigned long long dtb = ~0ull, vfix = 0ull, mine = 0ull;
-  if (i < i1) {
-    fi = s.f[i];
-    job = fi / MAXF;
-    const JobDev &J = B.jobs[job];
-    const Feat F = B.feat[fi];
-    const bool moving = F.type != T_SI && B.grp[fi].active;
-    const bool want = F.type != T_SI && (all || MODE == 1 || B.grp[fi].active);
-    act = FORCES && moving;
-    uint32_t count = 0;
-    const double4 xi = s.xh[i];
-    if (want) {
-      const Grid &G = J.G;
-      // scan reach: the cut-off radius, or the Verlet list's in MODE 1
-      const double ksup = MODE == 1 ? J.ksup_s : J.ksup;
-      double Rs = (MODE == 1 ? J.rfac_s : G.rfac) * xi.w;
-      const double rmax = MODE == 1 ? J.rmax_s : G.rmax;
-      Rs = Rs < rmax ? Rs : rmax;
-      const double pc[3] = {xi.x, xi.y, xi.z};
-      // cell levels that can hold a neighbour: h is L-Lipschitz, so a
-      // neighbour (r < R_i) has |h_j - h_i| <= L R_i (widened for rounding)
-      int lv0 = 0, lv1 = G.nlev - 1;
-      if (G.nlev > 1) {
-        const double dh = G.lip * Rs * (1.0 + 1e-9);
-        lv0 = h_level(G, (xi.w - dh) * (1.0 - 1e-12));
-        lv1 = h_level(G, (xi.w + dh) * (1.0 + 1e-12));
-      }
-      // features that bound fi (bit = local feature id); a candidate of fi's
-      // own feature interacts as "same", one of a bounding feature of the same
-      // job as "boundary".  The scan only visits cells of i's own job, so a
-      // candidate's feature slot is in i's job range and its local id is its
-      // low 6 bits.
-      const unsigned long long accept = B.bmask[fi] | (1ull << (fi & (MAXF - 1)));
-      const double kc2 = J.ksup2;   // c^2, c = support radius / h
-      const double A4 = kc2 * (xi.w * xi.w);
-      // Candidates are classified in FP32 from the scan records (which hold
-      // 2h) by the job's band (JobDev): a certain neighbour below H^2 band_in, a
-      // certain non-neighbour above H^2 band_out, H = 2 max(h_i, h_j); in
-      // between the exact FP64 predicate decides, so the classification always
-      // equals it
-      const float4 xif = scan_record<D>(xi, (uint32_t)fi);
-      const float Hif = D == 2 ? xif.z : xif.w;
-      float cin = J.band_in, cout = MODE == 1 ? J.band_reach : J.band_out;
-      if (__builtin_fabs(xi.x) > J.band_x || __builtin_fabs(xi.y) > J.band_x ||
-          (D == 3 && __builtin_fabs(xi.z) > J.band_x))
-        band_beyond<D, MODE>(J, xi, cin, cout);
-      static_assert(NB >= 1 && NB <= 8, "records are padded by 8");
-      // hits collect in the thread's own column of the LDS ring (entry-major,
-      // so the lanes of a wave hit distinct banks whatever their fill); each
-      // block of LB entries is stored as one 32-byte sector when full (and
-      // the last once more, partly filled, at the end).  One LDS write per
-      // hit replaces a select over LB registers, which every lane would
-      // execute whenever any lane of the wave hits.
-      static_assert(LB == 8, "the ring is flushed as two 16-byte stores");
-      uint4 *wp = reinterpret_cast<uint4 *>(MODE == 1 ? B.skin : nbr) + (size_t)i * (LB / 4);
-      const uint32_t wstep = (uint32_t)n * (LB / 4);
-      const uint32_t nblk = (uint32_t)(MODE == 1 ? B.skin_cap : B.cap) / LB;   // blocks of capacity
-      for (int lv = lv0; lv <= lv1; ++lv) {
-        // a level-lv candidate has h_j < hcap[lv], so none beyond
-        // c max(h_i, hcap[lv]) is a neighbour
-        double Rl = ksup * (xi.w > G.hcap[lv] ? xi.w : G.hcap[lv]) * (1.0 + 1e-9);
-        Rl = Rl < Rs ? Rl : Rs;
-        const double R2 = Rl * Rl;
-        int lo_c[3] = {0, 0, 0}, hi_c[3] = {0, 0, 0};
-#pragma unroll
-        for (int a = 1; a < D; ++a) {
-          lo_c[a] = cell_coord(G, lv, a, pc[a] - Rl);
-          hi_c[a] = cell_coord(G, lv, a, pc[a] + Rl);
-        }
-        // grid values the row loop needs, kept in registers
-        const double c0 = G.c[lv][0], inv0 = G.inv_c[lv][0], lo1 = G.lo[1], c1 = G.c[lv][1];
-        const double lo2 = D == 3 ? G.lo[2] : 0.0, c2 = D == 3 ? G.c[lv][2] : 0.0;
-        const uint32_t nc0 = (uint32_t)G.nc[lv][0];
-        const uint32_t cbase = G.cbase + G.lbase[lv];
-        const double u0 = (pc[0] - G.lo[0]) * inv0;     // x of i in cell units
-        const double top0 = (double)(G.nc[lv][0] - 1);
-        for (int cz = lo_c[2]; cz <= hi_c[2]; ++cz) {
-          double dz2 = 0.0;
-          if (D == 3) {
-            const double z0 = lo2 + cz * c2;
-            double dz = z0 - pc[2] > pc[2] - (z0 + c2) ? z0 - pc[2] : pc[2] - (z0 + c2);
-            dz = dz - 1e-7 * c2;
-            dz = dz > 0.0 ? dz : 0.0;
-            dz2 = dz * dz;
-          }
-          for (int cy = lo_c[1]; cy <= hi_c[1]; ++cy) {
-            const double y0 = lo1 + cy * c1;
-            double dy = y0 - pc[1] > pc[1] - (y0 + c1) ? y0 - pc[1] : pc[1] - (y0 + c1);
-            dy = dy - 1e-7 * c1;
-            dy = dy > 0.0 ? dy : 0.0;
-            const double w2 = R2 - dy * dy - dz2;
-            if (w2 < 0.0) continue;
-            // half chord of the row; the FP32 square root (error < 2e-7
-            // relative) is covered by the 1e-6 relative widening
-            const double wx = (double)sqrt_((float)w2) * (1.0 + 1e-6) + 1e-7 * c0;
-            const double wu = wx * inv0;
-            double t0 = __builtin_floor(u0 - wu), t1 = __builtin_floor(u0 + wu);
-            t0 = t0 >= 0.0 ? t0 : 0.0;   // also maps NaN to cell 0
-            t1 = t1 >= 0.0 ? t1 : 0.0;
-            t0 = t0 < top0 ? t0 : top0;
-            t1 = t1 < top0 ? t1 : top0;
-            const uint32_t row = cbase + cell_row<D>(G, lv, (uint32_t)cy, (uint32_t)cz) * nc0;
-            const uint32_t jb = cstart[row + (uint32_t)t0], je = cstart[row + (uint32_t)t1 + 1];
-            // NB candidates per pass: records loaded together (the arrays are
-            // padded by 8 past the capacity), the predicate evaluated for all of
-            // them without early exits, then the hits appended in order
-            for (uint32_t j0 = jb; j0 < je; j0 += NB) {
-              const float4 *rp = s.xf + j0;
-              float4 xr[NB];
-              uint32_t fr[NB];   // job-local feature id of the candidate
-  #pragma unroll
-              for (int q = 0; q < NB; ++q) {
-                xr[q] = rp[q];
-                fr[q] = __float_as_uint(xr[q].w) & (MAXF - 1);
-              }
-              uint32_t tag[NB];
-  #pragma unroll
-              for (int q = 0; q < NB; ++q) {
-                const uint32_t j = j0 + q;
-                const bool rel = (accept >> (fr[q] & (MAXF - 1))) & 1ull;
-                const bool cand = rel & (j < je) & (j != (uint32_t)i);
-                const float ex = xif.x - xr[q].x, ey = xif.y - xr[q].y;
-                const float ez = D == 3 ? xif.z - xr[q].z : 0.0f;
-                const float d2 = ex * ex + ey * ey + ez * ez;
-                const float Hj = D == 2 ? xr[q].z : xr[q].w;
-                const float H = __builtin_fmaxf(Hif, Hj);
-                const float H2 = H * H;
-                const float tin = H2 * cin, tout = H2 * cout;
-                bool hit;
-                if constexpr (MODE == 1) {   // Verlet list: all that may lie within reach
-                  hit = cand & !(d2 > tout);
-                } else {
-                  hit = cand & (d2 < tin);
-                  if (cand & !(d2 < tin) & !(d2 > tout))   // near the support radius: exact test
-                    hit = within_a4<D>(xi, A4, kc2, s.xh[j]);
-                }
-                tag[q] = hit ? (j | (fr[q] == (uint32_t)(fi & (MAXF - 1)) ? 0u : 0x80000000u))
-                             : 0xffffffffu;
-              }
-              append_hits<NB, LR>(tag, &ring[0][col], BLOCK, count, wp, wstep, nblk);
-            }
-          }
-        }
-      }
-      if (count % LB != 0 && count / LB < nblk) {   // the last, partly filled block
-        const uint32_t k0 = (count / LB * LB) % LR;
-        wp[0] = make_uint4(ring[k0][col], ring[k0 + 1][col], ring[k0 + 2][col], ring[k0 + 3][col]);
-        wp[1] = make_uint4(ring[k0 + 4][col], ring[k0 + 5][col], ring[k0 + 6][col], ring[k0 + 7][col]);
-      }
-      if (MODE == 1 && (int)count > B.skin_cap) {
-        atomicMax(&B.st[job].skin_max, count);
-        atomicExch(&B.st[job].skin_overflow, 1u);
-        count = B.skin_cap;
-      } else if (MODE != 1 && (int)count > B.cap) {
-        atomicMax(&B.st[job].overflow_max, count);
-        atomicExch(&B.st[job].overflow, 1u);
-        count = B.cap;
-      }
-    }
-    if (FORCES && act) {
-      const int k = F.k;
-      double4 v4 = s.v[i];
-      if (B.grp[fi].reset_now) {
-        v4 = make_double4(0.0, 0.0, 0.0, 0.0);
-        s.v[i] = v4;
-      }
-      const BNorm *bnrow = B.bn + (size_t)fi * MAXF;
-      // a 3D patch of a level set with imported curves: pair-dependent normals
-      const bool pairn = D == 3 && F.kind == K_LEVEL && J.g.cpts != nullptr;
-      double S, gam, Pi[3], B3[3];
-      if (k == D)
-        sweep_a_sums<D, D, R, CMP>(J.g, s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, fi, pairn, S, gam, Pi, B3,
-                                        LDS_SUMS ? &ring[0][col] : nullptr, LR, BLOCK);
-      else if (k == D - 1)
-        sweep_a_sums<D, D - 1, R, CMP>(J.g, s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, fi, pairn, S, gam, Pi, B3,
-                                        LDS_SUMS ? &ring[0][col] : nullptr, LR, BLOCK);
-      else
-        sweep_a_sums<D, 1, R, CMP>(J.g, s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, fi, pairn, S, gam, Pi, B3,
-                                        LDS_SUMS ? &ring[0][col] : nullptr, LR, BLOCK);
-      // the FP32 modes store a^p in FP32 and hold V~ and the time steps to
-      // 1e-5: FP32 reciprocals and roots suffice there (relative error 2^-23)
-      constexpr bool F32 = sizeof(R) == 4;
-      double a3[3] = {0.0, 0.0, 0.0};
-      const double ig = F32 ? (double)rcp_((float)gam) : 0.0;
-#pragma unroll
-      for (int a = 0; a < D; ++a) a3[a] = F32 ? -((Pi[a] + B3[a]) * ig) : -((Pi[a] + B3[a]) / gam);
-      double xa[3] = {xi.x, xi.y, xi.z};
-      tangent_at<D>(J.g, F, xa, B.enrm, i, a3);
-      // in 2D the record's free slots carry v^n (after any reset) in the
-      // sweep precision, so sweep B gathers one record per neighbour less
-      R4 o;
-      o.x = (R)a3[0];
-      o.y = (R)a3[1];
-      o.z = D == 2 ? (R)v4.x : (R)a3[2];
-      o.w = D == 2 ? (R)v4.y : R(0);
-      const double vt = F32 ? (double)rcp_((float)S) : 1.0 / S;
-      ap[i] = o;
-      if (dbg_gam) dbg_gam[i] = gam;
-      if (dbg_vt) dbg_vt[i] = vt;
-      // Eq. (fa_time_step_size) terms from a^p and v^n
-      const double rc = J.ksup * xi.w;
-      const double dt = step_terms<F32>(rc, a3[0] * a3[0] + a3[1] * a3[1] + a3[2] * a3[2],
-                                        v4.x * v4.x + v4.y * v4.y + v4.z * v4.z);
-      dtb = dbits(dt);
-      vfix = (unsigned long long)__builtin_llrint(vt * B.grp[fi].vscale);
-    } else if (FORCES) {
-      R4 z;
-      z.x = z.y = z.z = z.w = R(0);
-      ap[i] = z;
-      if (dbg_gam) dbg_gam[i] = 0.0;
-      if (dbg_vt) dbg_vt[i] = 0.0;
-    }
-    if (MODE == 1) {
-      B.nsk[i] = count;
-    } else {
-      nnb[i] = count;
-      mine = count;
-    }
-  }
-  if (FORCES) {
-    wave_commit(act, fi, dtb, vfix, B.smin, DT1, B.ssum);
-    wave_count(i < i1 && mine != 0ull, job, mine, B.scnt, SC_PAIRS);
-  }
-}
-
-// A position of u cells along an axis as whole cells and a fraction.  A
-// particle the caller put 2^30 cells or farther off the grid (of at most 2^29
-// cells) is taken to be that far off: its ranges end in the same border cells,
-// and a whole part plus a half chord stays an int.  So is a NaN, which has no
-// neighbours.
-__host__ __device__ __forceinline__ void cell_split(double u, int &whole, float &frac) {
-  constexpr double FAR = 1073741824.0;
-  u = __builtin_fmax(__builtin_fmin(u, FAR), -FAR);
-  const double f = __builtin_floor(u);
-  whole = (int)f;
-  frac = (float)(u - f);
-}
-// the cells [t0, t1] of a row of nc that a half chord of w cells about that position touches
-__host__ __device__ __forceinline__ void row_range(int whole, float frac, float w, int nc, int &t0, int &t1) {
-  w = __builtin_fminf(w, 1e9f);
-  t0 = whole + (int)__builtin_floorf(frac - w);
-  t1 = whole + (int)__builtin_floorf(frac + w);
-  t0 = t0 > 0 ? (t0 < nc - 1 ? t0 : nc - 1) : 0;
-  t1 = t1 > 0 ? (t1 < nc - 1 ? t1 : nc - 1) : 0;
-}
-
-// a word of a record that no kernel of the launch writes, at an address all
-// lanes of the wave share: one scalar load, and no vector register
-template <typename T>
-__device__ __forceinline__ T sload(const T &v) {
-  return *(const T __attribute__((address_space(4))) *)(uintptr_t)&v;
-}
-
-// ---------------------------------------------------------------------------
-// lanes of one group of G (aligned) exchange values by DPP
-// ---------------------------------------------------------------------------
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const unsigned long long b = dbits(v);
-  const uint32_t lo = dpp_u32<CTRL>((uint32_t)b), hi = dpp_u32<CTRL>((uint32_t)(b >> 32));
-  return bitsd(((unsigned long long)hi << 32) | lo);
-}
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_SHR1 = 0x111,
-              DPP_SHR2 = 0x112, DPP_SHR4 = 0x114;
-// sum over the group, the same bits in every lane (each step adds the same
-// two partial sums in either order)
-template <int G>
-__device__ __forceinline__ double group_sum(double v) {
-  v += dpp_f64<DPP_XOR1>(v);
-  if (G >= 4) v += dpp_f64<DPP_XOR2>(v);
-  if (G == 8) v += dpp_f64<DPP_HALF_MIRROR>(v);
-  return v;
-}
-template <int G>
-__device__ __forceinline__ uint32_t group_or(uint32_t v) {
-  v |= dpp_u32<DPP_XOR1>(v);
-  if (G >= 4) v |= dpp_u32<DPP_XOR2>(v);
-  if (G == 8) v |= dpp_u32<DPP_HALF_MIRROR>(v);
-  return v;
-}
-// inclusive prefix sum over the group's lanes (gl the lane in the group)
-template <int G>
-__device__ __forceinline__ uint32_t group_scan(uint32_t v, int gl) {
-  uint32_t t = dpp_u32<DPP_SHR1>(v);
-  v += gl >= 1 ? t : 0u;
-  if (G >= 4) {
-    t = dpp_u32<DPP_SHR2>(v);
-    v += gl >= 2 ? t : 0u;
-  }
-  if (G == 8) {
-    t = dpp_u32<DPP_SHR4>(v);
-    v += gl >= 4 ? t : 0u;
-  }
-  return v;
-}
-
-// does v hold in a lane of the wave
-__device__ __forceinline__ bool any_lane(bool v) { return __builtin_amdgcn_ballot_w64(v) != 0ull; }
-
-// The sums of sweep_a_sums by G lanes: lane l takes the entries l, l + G, ...,
-// NB of them at a time, and the caller adds the lanes' sums.
-using LdsList = const __attribute__((address_space(3))) uint32_t *;
 template <int D, int K, typename R, bool CMP, bool PN, int NB, int G>
-__device__ __forceinline__ void group_sums(const Geom &g, const Parts &s,
+__host__ __device__ __forceinline__ void group_sums(const Geom &g, const Parts &s,
                                              const double4 *__restrict__ enrm,
                                              const BNorm *__restrict__ bnrow, int bw, double p0,
                                              double klen, double bscale,
@@ -1364,6 +758,553 @@ __device__ __forceinline__ void group_sums(const Geom &g, const Parts &s,
   }
 }
 
+// The same sums by the one lane of k_nbr_forces (2D), in list order.  With
+// nlanes > 1, and in 3D, which has no such kernel: those of lane `lane` of
+// k_nbr_group (host callers).
+template <int D, int K, typename R, bool CMP>
+__host__ __device__ __forceinline__ void sweep_a_sums(const Geom &g, const Parts &s,
+                                             const double4 *__restrict__ enrm,
+                                             const BNorm *__restrict__ bnrow, int bw, double p0,
+                                             double klen, double bscale,
+                                             const uint32_t *__restrict__ nbr, int n, int i,
+                                             uint32_t cnt, const double4 &xi, int fi, bool pair_normals,
+                                             double &S, double &gam, double Pi[3], double B[3],
+                                             const uint32_t *ring = nullptr, uint32_t ring_len = 0,
+                                             uint32_t ring_stride = 0, uint32_t lane = 0,
+                                             uint32_t nlanes = 1) {
+  if (D == 3 || nlanes > 1) {
+    auto split = [&](auto lanes) {
+      group_sums<D, K, R, CMP, true, 4, decltype(lanes)::value>(g, s, enrm, bnrow, bw, p0, klen, bscale, nbr, n, i,
+                                                                cnt, xi, pair_normals, S, gam, Pi, B, nullptr, 0,
+                                                                lane);
+    };
+    if (nlanes <= 1) split(std::integral_constant<int, 1>());
+    else if (nlanes == 2) split(std::integral_constant<int, 2>());
+    else if (nlanes == 4) split(std::integral_constant<int, 4>());
+    else split(std::integral_constant<int, 8>());
+    return;
+  }
+  // h enters rho_t = h^-k; the kernel is evaluated at the smoothing length
+  // klen h (cut-off radius 2 klen h)
+  const R hi = (R)xi.w;
+  const R kl = (R)klen;
+  const R ihi = rcp_((R)(klen * xi.w));
+  constexpr R alpha = kalphaK<K, R>();
+  const R hik = powK<K>(hi), hi2k = hik * hik;
+  const R ihik = powK<K>(ihi);
+  const R P0 = (R)p0;
+  const R wself = alpha * ihik;
+  Sum<CMP> aS, aG, aP[2], aB[2];
+  aS.init((double)wself);
+  aG.init((double)(wself * hik));
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    aP[a].init(0.0);
+    aB[a].init(0.0);
+  }
+  constexpr int NB = SPH_NBATCH;
+  static_assert(NB == 4 || NB == LB, "record batches of 4 or 8 tile a list block");
+  // records gathered together: GB of a batch's NB (fewer live registers)
+  constexpr int GB = SPH_GBATCH < NB ? SPH_GBATCH : NB;
+  static_assert(NB % GB == 0, "gather groups tile a batch");
+  // The list's last entries may also sit in the caller's LDS ring (entry e
+  // in slot e % ring_len, column stride ring_stride): entries from lbase on
+  // are read there, the ones before from the list in memory (whole blocks,
+  // as lbase is a multiple of LB).  Either way every entry is read in list
+  // order, so the sums are the same.
+  uint32_t lbase = cnt;
+  if (ring != nullptr) lbase = cnt > ring_len ? (cnt - ring_len + LB - 1) / LB * LB : 0u;
+  const uint4 *gl = reinterpret_cast<const uint4 *>(nbr) + (size_t)i * (LB / 4);
+  for (uint32_t e0 = 0; e0 < cnt; e0 += NB) {
+    {
+      uint32_t u[NB];
+      if (e0 < lbase) {   // NB entries of a block in memory: 16-byte loads
+#pragma unroll
+        for (int h = 0; h < NB / 4; ++h) {
+          const uint4 w = gl[(size_t)(e0 / LB) * n * (LB / 4) + (e0 % LB) / 4 + h];
+          u[4 * h] = w.x;
+          u[4 * h + 1] = w.y;
+          u[4 * h + 2] = w.z;
+          u[4 * h + 3] = w.w;
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < NB; ++q) u[q] = ring[((e0 + q) % ring_len) * ring_stride];
+      }
+#pragma unroll
+      for (int q = 0; q < NB; ++q) u[q] = e0 + q < cnt ? u[q] : 0u;
+#pragma unroll
+      for (int g0 = 0; g0 < NB; g0 += GB) {
+      double4 xr[GB];
+#pragma unroll
+      for (int q = 0; q < GB; ++q) xr[q] = s.xh[u[g0 + q] & 0x7fffffffu];
+#pragma unroll
+      for (int qg = 0; qg < GB; ++qg) {
+        const int q = g0 + qg;
+        if (e0 + q >= cnt) break;
+        const double4 xj = xr[qg];
+        const R dx0 = (R)(xi.x - xj.x), dx1 = (R)(xi.y - xj.y);
+        const R rr = sqrt_(dx0 * dx0 + dx1 * dx1);
+        const R hj = (R)xj.w;
+        const R hjk = powK<K>(hj);
+        const R hsum = hi2k + hjk * hjk;
+        const R ihij = rcp_(kl * (R(0.5) * (hi + hj)));
+        const R qij = rr * ihij;
+        if (!(u[q] >> 31)) {
+          const R w = alpha * wshapeK<K>(rr * ihi) * ihik;           // W(r, h_i)
+          aS.add(w);
+          aG.add(w * hjk);
+          const R ih2 = ihij * ihij;
+          const R ihk2 = K == 1 ? ih2 * ihij : (K == 2 ? ih2 * ih2 : ih2 * ih2 * ihij);
+          const R c = P0 * hsum * alpha * dwqK<K>(qij) * ihk2;       // (dW/dr)/r at h_ij
+          aP[0].add(c * dx0);
+          aP[1].add(c * dx1);
+        } else {
+          // the particle volume (Eq. (particle_volume)) is the inverse of i's
+          // number density: the boundary particles that act on i count too
+          aS.add(alpha * wshapeK<K>(rr * ihi) * ihik);
+          double nv[2];
+          if constexpr (K == D) {   // the volume: the domain's normal k_rank_gather stored at b
+            const double4 e = enrm[u[q] & 0x7fffffffu];
+            nv[0] = e.x;
+            nv[1] = e.y;
+          } else {
+            const int fj = s.f[u[q] & 0x7fffffffu];
+            const BNorm N = bnrow[fj & (MAXF - 1)];
+            if (N.mode >= 2) {   // a curved boundary: the normal k_rank_gather stored
+              const double4 e = enrm[u[q] & 0x7fffffffu];
+              nv[0] = e.x;
+              nv[1] = e.y;
+              } else {
+              nv[0] = N.n[0];
+              nv[1] = N.n[1];
+            }
+          }
+          const R om = (bw == 0 ? rcp_(hj) : (bw == 1 ? powK<K>(hj) * rcp_(hj) : R(0))) * (R)bscale;
+          const R w = alpha * wshapeK<K>(qij) * powK<K>(ihij);          // W(r, h_ib)
+          if constexpr (CMP) {   // FP32 terms: the normal rounded to FP32
+            const float c = (float)(P0 * hsum * w * om);
+            aB[0].add(c * (float)nv[0]);
+            aB[1].add(c * (float)nv[1]);
+          } else {
+            const double c = (double)(P0 * hsum * w * om);
+            aB[0].add(c * nv[0]);
+            aB[1].add(c * nv[1]);
+          }
+        }
+      }
+      }
+    }
+  }
+  S = aS.get();
+  gam = aG.get();
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    Pi[a] = aP[a].get();
+    B[a] = aB[a].get();
+  }
+  Pi[2] = B[2] = 0.0;
+}
+
+// Appends the hits among tag[0, NB) (0xffffffff: no hit) to a particle's
+// column of the LDS ring (slot k at rc[k * stride], slot = entry mod LR) and
+// stores each list block they complete to *wp as two 16-byte writes, while
+// the capacity of nblk blocks allows.  With a ring of two blocks or more the
+// block a batch completes is still whole after the batch (NB <= LB hits
+// reach at most LB - 1 entries into the next block), so the test for a
+// store runs once per batch instead of once per hit.
+template <int NB, int LR>
+__host__ __device__ __forceinline__ void append_hits(const uint32_t (&tag)[NB], uint32_t *rc,
+                                                     int stride, uint32_t &count, uint4 *&wp,
+                                                     uint32_t wstep, uint32_t nblk) {
+  static_assert(NB <= LB && LR % LB == 0, "a batch completes at most one block");
+  if constexpr (LR >= 2 * LB) {
+    const uint32_t c0 = count;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      if (tag[q] != 0xffffffffu) {
+        rc[(count % LR) * stride] = tag[q];
+        ++count;
+      }
+    }
+    if (count / LB != c0 / LB && count / LB <= nblk) {
+      const uint32_t k0 = (c0 / LB * LB) % LR;
+      wp[0] = make_uint4(rc[k0 * stride], rc[(k0 + 1) * stride], rc[(k0 + 2) * stride],
+                         rc[(k0 + 3) * stride]);
+      wp[1] = make_uint4(rc[(k0 + 4) * stride], rc[(k0 + 5) * stride], rc[(k0 + 6) * stride],
+                         rc[(k0 + 7) * stride]);
+      wp += wstep;
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      if (tag[q] != 0xffffffffu) {
+        const uint32_t k = count % LR;
+        rc[k * stride] = tag[q];
+        ++count;
+        if (k % LB == LB - 1 && count / LB <= nblk) {
+          const uint32_t k0 = k - (LB - 1);
+          wp[0] = make_uint4(rc[k0 * stride], rc[(k0 + 1) * stride], rc[(k0 + 2) * stride],
+                             rc[(k0 + 3) * stride]);
+          wp[1] = make_uint4(rc[(k0 + 4) * stride], rc[(k0 + 5) * stride], rc[(k0 + 6) * stride],
+                             rc[(k0 + 7) * stride]);
+          wp += wstep;
+        }
+      }
+    }
+  }
+}
+
+// the classification's band (JobDev) of a particle that lies outside its job's
+// box, where the caller may have put it
+template <int D, int MODE>
+__device__ __forceinline__ void band_beyond(const JobDev &J, const double4 &xi, float &cin, float &cout) {
+  double xb = __builtin_fabs(xi.x);
+  xb = __builtin_fabs(xi.y) > xb ? __builtin_fabs(xi.y) : xb;
+  if (D == 3) xb = __builtin_fabs(xi.z) > xb ? __builtin_fabs(xi.z) : xb;
+  xb += 2.0 * J.rmax_s + 2.0 * J.G.cmax;
+  const double w = (D == 2 ? 2e-6 : 2e-5) +
+                   (D == 3 ? 1.7320508075688772 : 1.4142135623730951) * 0x1p-23 * xb * 1.01 * J.iband;
+  const double k = MODE == 1 ? 0.5 * J.ksup_s : J.klen;
+  cin = w < 1.0 ? (float)((1.0 - w) * (1.0 - w) * k * k) : -1.0f;
+  cout = (float)((1.0 + w) * (1.0 + w) * k * k);
+}
+
+// ---------------------------------------------------------------------------
+// neighbour list (Algorithm 1 "construct Verlet neighbor list") and, in the
+// same launch, sweep A over it; FORCES = false builds lists only.  Two kernels
+// make the same lists: k_nbr_forces, one lane per particle, and k_nbr_group, G
+// lanes per particle.  The candidate scan covers, for every cell row within
+// R_i of x_i, only the cells under the chord of the disc (sphere) of radius
+// R_i, so no neighbour is skipped and fewer non-neighbours are tested.  The pair
+// sums then run over the list just written, so the force math executes once
+// per neighbour instead of once per candidate.  Every particle reads its own
+// job's geometry and grid; cells of different jobs never meet.
+//
+// k_nbr_forces: one lane per particle of the slots [i0, i1).  It is the faster
+// for large 2D jobs (launch_nbr_forces), whose short lists do not fill several
+// lanes: of 1,000,000 particles, FP32, cell scan, 119 us against 135 with 2
+// lanes and 157 with 4; the list build 170 against 225 us.
+// MODE 0: candidates from the cell scan, as above.  MODE 1 (FORCES = false,
+// only when a rebuild is due): the Verlet candidate list of every
+// non-singular particle, the cell scan at the reach (c + delta) h with the
+// FP32 test alone, widened by its error bound so that it keeps every pair
+// within that reach.
+// ---------------------------------------------------------------------------
+template <typename R, bool FORCES, int NB, bool CMP, int MODE>
+__global__ __launch_bounds__(BLOCK) void k_nbr_forces(
+    Batch B, Parts s, const uint32_t *__restrict__ cstart, int all, uint32_t *__restrict__ nbr,
+    uint32_t *__restrict__ nnb, typename Vec4<R>::T *__restrict__ ap,
+    double *__restrict__ dbg_gam, double *__restrict__ dbg_vt, Parts home, int i0, int i1) {
+  constexpr int D = 2;
+  static_assert(MODE == 0 || (MODE == 1 && !FORCES), "candidate list modes");
+  if (MODE == 1) {
+    if (B.vstate[VS_REBUILD] == 0ull) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) B.vstate[VS_BUILDS] += 1ull;
+    // s holds the particles just sorted; they go back to the buffer the
+    // steps use between rebuilds (no kernel of this launch reads it)
+    const int c = i0 + xcd_block() * BLOCK + (int)threadIdx.x;
+    if (c < i1) {
+      home.xh[c] = s.xh[c];
+      home.v[c] = s.v[c];
+      home.f[c] = s.f[c];
+      home.oid[c] = s.oid[c];
+      home.xf[c] = s.xf[c];
+    }
+  }
+  using R4 = typename Vec4<R>::T;
+  // hits collect in the thread's own column of an LDS ring of LR entries (a
+  // multiple of LB; see the append below); it keeps the last LR entries, so
+  // that in the FP32 modes a list no longer than LR stays whole in LDS,
+  // where the pair sums read it (the FP64 sums read the list from memory:
+  // the ring's addressing would cost them a wave per SIMD); the Verlet build
+  // keeps two blocks, so that its block stores are tested once per batch
+  constexpr bool LDS_SUMS = FORCES && sizeof(R) == 4;
+  constexpr int LR = LDS_SUMS ? SPH_LDS_LIST : (MODE == 1 ? 2 * LB : LB);
+  static_assert(LR % LB == 0, "the ring holds whole blocks");
+  __shared__ uint32_t ring[LR][BLOCK];
+  const int col = (int)threadIdx.x;
+  const int n = B.n;
+  const int i = i0 + xcd_block() * BLOCK + (int)threadIdx.x;
+  bool act = false;
+  int fi = 0, job = 0;
+  unsigned long long dtb = ~0ull, vfix = 0ull, mine = 0ull;
+  if (i < i1) {
+    fi = s.f[i];
+    job = fi / MAXF;
+    const JobDev &J = B.jobs[job];
+    const Feat F = B.feat[fi];
+    const bool moving = F.type != T_SI && B.grp[fi].active;
+    const bool want = F.type != T_SI && (all || MODE == 1 || B.grp[fi].active);
+    act = FORCES && moving;
+    uint32_t count = 0;
+    const double4 xi = s.xh[i];
+    if (want) {
+      const Grid &G = J.G;
+      // scan reach: the cut-off radius, or the Verlet list's in MODE 1
+      const double ksup = MODE == 1 ? J.ksup_s : J.ksup;
+      double Rs = (MODE == 1 ? J.rfac_s : G.rfac) * xi.w;
+      const double rmax = MODE == 1 ? J.rmax_s : G.rmax;
+      Rs = Rs < rmax ? Rs : rmax;
+      const double pc[2] = {xi.x, xi.y};
+      // cell levels that can hold a neighbour: h is L-Lipschitz, so a
+      // neighbour (r < R_i) has |h_j - h_i| <= L R_i (widened for rounding)
+      int lv0 = 0, lv1 = G.nlev - 1;
+      if (G.nlev > 1) {
+        const double dh = G.lip * Rs * (1.0 + 1e-9);
+        lv0 = h_level(G, (xi.w - dh) * (1.0 - 1e-12));
+        lv1 = h_level(G, (xi.w + dh) * (1.0 + 1e-12));
+      }
+      // features that bound fi (bit = local feature id); a candidate of fi's
+      // own feature interacts as "same", one of a bounding feature of the same
+      // job as "boundary".  The scan only visits cells of i's own job, so a
+      // candidate's feature slot is in i's job range and its local id is its
+      // low 6 bits.
+      const unsigned long long accept = B.bmask[fi] | (1ull << (fi & (MAXF - 1)));
+      const double kc2 = J.ksup2;   // c^2, c = support radius / h
+      const double A4 = kc2 * (xi.w * xi.w);
+      // Candidates are classified in FP32 from the scan records (which hold
+      // 2h) by the job's band (JobDev): a certain neighbour below H^2 band_in, a
+      // certain non-neighbour above H^2 band_out, H = 2 max(h_i, h_j); in
+      // between the exact FP64 predicate decides, so the classification always
+      // equals it
+      const float4 xif = scan_record<D>(xi, (uint32_t)fi);
+      const float Hif = xif.z;
+      float cin = J.band_in, cout = MODE == 1 ? J.band_reach : J.band_out;
+      if (__builtin_fabs(xi.x) > J.band_x || __builtin_fabs(xi.y) > J.band_x)
+        band_beyond<D, MODE>(J, xi, cin, cout);
+      static_assert(NB >= 1 && NB <= 8, "records are padded by 8");
+      // hits collect in the thread's own column of the LDS ring (entry-major,
+      // so the lanes of a wave hit distinct banks whatever their fill); each
+      // block of LB entries is stored as one 32-byte sector when full (and
+      // the last once more, partly filled, at the end).  One LDS write per
+      // hit replaces a select over LB registers, which every lane would
+      // execute whenever any lane of the wave hits.
+      static_assert(LB == 8, "the ring is flushed as two 16-byte stores");
+      uint4 *wp = reinterpret_cast<uint4 *>(MODE == 1 ? B.skin : nbr) + (size_t)i * (LB / 4);
+      const uint32_t wstep = (uint32_t)n * (LB / 4);
+      const uint32_t nblk = (uint32_t)(MODE == 1 ? B.skin_cap : B.cap) / LB;   // blocks of capacity
+      for (int lv = lv0; lv <= lv1; ++lv) {
+        // a level-lv candidate has h_j < hcap[lv], so none beyond
+        // c max(h_i, hcap[lv]) is a neighbour
+        double Rl = ksup * (xi.w > G.hcap[lv] ? xi.w : G.hcap[lv]) * (1.0 + 1e-9);
+        Rl = Rl < Rs ? Rl : Rs;
+        const double R2 = Rl * Rl;
+        const int ylo = cell_coord(G, lv, 1, pc[1] - Rl), yhi = cell_coord(G, lv, 1, pc[1] + Rl);
+        // grid values the row loop needs, kept in registers
+        const double c0 = G.c[lv][0], inv0 = G.inv_c[lv][0], lo1 = G.lo[1], c1 = G.c[lv][1];
+        const uint32_t nc0 = (uint32_t)G.nc[lv][0];
+        const uint32_t cbase = G.cbase + G.lbase[lv];
+        const double u0 = (pc[0] - G.lo[0]) * inv0;     // x of i in cell units
+        const double top0 = (double)(G.nc[lv][0] - 1);
+        for (int cy = ylo; cy <= yhi; ++cy) {
+          const double y0 = lo1 + cy * c1;
+          double dy = y0 - pc[1] > pc[1] - (y0 + c1) ? y0 - pc[1] : pc[1] - (y0 + c1);
+          dy = dy - 1e-7 * c1;
+          dy = dy > 0.0 ? dy : 0.0;
+          const double w2 = R2 - dy * dy;
+          if (w2 < 0.0) continue;
+          // half chord of the row; the FP32 square root (error < 2e-7
+          // relative) is covered by the 1e-6 relative widening
+          const double wx = (double)sqrt_((float)w2) * (1.0 + 1e-6) + 1e-7 * c0;
+          const double wu = wx * inv0;
+          double t0 = __builtin_floor(u0 - wu), t1 = __builtin_floor(u0 + wu);
+          t0 = t0 >= 0.0 ? t0 : 0.0;   // also maps NaN to cell 0
+          t1 = t1 >= 0.0 ? t1 : 0.0;
+          t0 = t0 < top0 ? t0 : top0;
+          t1 = t1 < top0 ? t1 : top0;
+          const uint32_t row = cbase + cell_row<D>(G, lv, (uint32_t)cy, 0u) * nc0;
+          const uint32_t jb = cstart[row + (uint32_t)t0], je = cstart[row + (uint32_t)t1 + 1];
+          // NB candidates per pass: records loaded together (the arrays are
+          // padded by 8 past the capacity), the predicate evaluated for all of
+          // them without early exits, then the hits appended in order
+          for (uint32_t j0 = jb; j0 < je; j0 += NB) {
+            const float4 *rp = s.xf + j0;
+            float4 xr[NB];
+            uint32_t fr[NB];   // job-local feature id of the candidate
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+              xr[q] = rp[q];
+              fr[q] = __float_as_uint(xr[q].w) & (MAXF - 1);
+            }
+            uint32_t tag[NB];
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+              const uint32_t j = j0 + q;
+              const bool rel = (accept >> (fr[q] & (MAXF - 1))) & 1ull;
+              const bool cand = rel & (j < je) & (j != (uint32_t)i);
+              const float ex = xif.x - xr[q].x, ey = xif.y - xr[q].y;
+              const float d2 = ex * ex + ey * ey;
+              const float H = __builtin_fmaxf(Hif, xr[q].z);
+              const float H2 = H * H;
+              const float tin = H2 * cin, tout = H2 * cout;
+              bool hit;
+              if constexpr (MODE == 1) {   // Verlet list: all that may lie within reach
+                hit = cand & !(d2 > tout);
+              } else {
+                hit = cand & (d2 < tin);
+                if (cand & !(d2 < tin) & !(d2 > tout))   // near the support radius: exact test
+                  hit = within_a4<D>(xi, A4, kc2, s.xh[j]);
+              }
+              tag[q] = hit ? (j | (fr[q] == (uint32_t)(fi & (MAXF - 1)) ? 0u : 0x80000000u))
+                           : 0xffffffffu;
+            }
+            append_hits<NB, LR>(tag, &ring[0][col], BLOCK, count, wp, wstep, nblk);
+          }
+        }
+      }
+      if (count % LB != 0 && count / LB < nblk) {   // the last, partly filled block
+        const uint32_t k0 = (count / LB * LB) % LR;
+        wp[0] = make_uint4(ring[k0][col], ring[k0 + 1][col], ring[k0 + 2][col], ring[k0 + 3][col]);
+        wp[1] = make_uint4(ring[k0 + 4][col], ring[k0 + 5][col], ring[k0 + 6][col], ring[k0 + 7][col]);
+      }
+      if (MODE == 1 && (int)count > B.skin_cap) {
+        atomicMax(&B.st[job].skin_max, count);
+        atomicExch(&B.st[job].skin_overflow, 1u);
+        count = B.skin_cap;
+      } else if (MODE != 1 && (int)count > B.cap) {
+        atomicMax(&B.st[job].overflow_max, count);
+        atomicExch(&B.st[job].overflow, 1u);
+        count = B.cap;
+      }
+    }
+    if (FORCES && act) {
+      const int k = F.k;
+      double4 v4 = s.v[i];
+      if (B.grp[fi].reset_now) {
+        v4 = make_double4(0.0, 0.0, 0.0, 0.0);
+        s.v[i] = v4;
+      }
+      const BNorm *bnrow = B.bn + (size_t)fi * MAXF;
+      double S, gam, Pi[3], B3[3];
+      if (k == D)
+        sweep_a_sums<D, D, R, CMP>(J.g, s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, fi, false, S, gam, Pi, B3,
+                                        LDS_SUMS ? &ring[0][col] : nullptr, LR, BLOCK);
+      else
+        sweep_a_sums<D, 1, R, CMP>(J.g, s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, fi, false, S, gam, Pi, B3,
+                                        LDS_SUMS ? &ring[0][col] : nullptr, LR, BLOCK);
+      // the FP32 modes store a^p in FP32 and hold V~ and the time steps to
+      // 1e-5: FP32 reciprocals and roots suffice there (relative error 2^-23)
+      constexpr bool F32 = sizeof(R) == 4;
+      double a3[3] = {0.0, 0.0, 0.0};
+      const double ig = F32 ? (double)rcp_((float)gam) : 0.0;
+#pragma unroll
+      for (int a = 0; a < D; ++a) a3[a] = F32 ? -((Pi[a] + B3[a]) * ig) : -((Pi[a] + B3[a]) / gam);
+      double xa[3] = {xi.x, xi.y, xi.z};
+      tangent_at<D>(J.g, F, xa, B.enrm, i, a3);
+      // in 2D the record's free slots carry v^n (after any reset) in the
+      // sweep precision, so sweep B gathers one record per neighbour less
+      R4 o;
+      o.x = (R)a3[0];
+      o.y = (R)a3[1];
+      o.z = (R)v4.x;
+      o.w = (R)v4.y;
+      const double vt = F32 ? (double)rcp_((float)S) : 1.0 / S;
+      ap[i] = o;
+      if (dbg_gam) dbg_gam[i] = gam;
+      if (dbg_vt) dbg_vt[i] = vt;
+      // Eq. (fa_time_step_size) terms from a^p and v^n
+      const double rc = J.ksup * xi.w;
+      const double dt = step_terms<F32>(rc, a3[0] * a3[0] + a3[1] * a3[1] + a3[2] * a3[2],
+                                        v4.x * v4.x + v4.y * v4.y + v4.z * v4.z);
+      dtb = dbits(dt);
+      vfix = (unsigned long long)__builtin_llrint(vt * B.grp[fi].vscale);
+    } else if (FORCES) {
+      R4 z;
+      z.x = z.y = z.z = z.w = R(0);
+      ap[i] = z;
+      if (dbg_gam) dbg_gam[i] = 0.0;
+      if (dbg_vt) dbg_vt[i] = 0.0;
+    }
+    if (MODE == 1) {
+      B.nsk[i] = count;
+    } else {
+      nnb[i] = count;
+      mine = count;
+    }
+  }
+  if (FORCES) {
+    wave_commit(act, fi, dtb, vfix, B.smin, DT1, B.ssum);
+    wave_count(i < i1 && mine != 0ull, job, mine, B.scnt, SC_PAIRS);
+  }
+}
+
+// A position of u cells along an axis as whole cells and a fraction.  A
+// particle the caller put 2^30 cells or farther off the grid (of at most 2^29
+// cells) is taken to be that far off: its ranges end in the same border cells,
+// and a whole part plus a half chord stays an int.  So is a NaN, which has no
+// neighbours.
+__host__ __device__ __forceinline__ void cell_split(double u, int &whole, float &frac) {
+  constexpr double FAR = 1073741824.0;
+  u = __builtin_fmax(__builtin_fmin(u, FAR), -FAR);
+  const double f = __builtin_floor(u);
+  whole = (int)f;
+  frac = (float)(u - f);
+}
+// the cells [t0, t1] of a row of nc that a half chord of w cells about that position touches
+__host__ __device__ __forceinline__ void row_range(int whole, float frac, float w, int nc, int &t0, int &t1) {
+  w = __builtin_fminf(w, 1e9f);
+  t0 = whole + (int)__builtin_floorf(frac - w);
+  t1 = whole + (int)__builtin_floorf(frac + w);
+  t0 = t0 > 0 ? (t0 < nc - 1 ? t0 : nc - 1) : 0;
+  t1 = t1 > 0 ? (t1 < nc - 1 ? t1 : nc - 1) : 0;
+}
+
+// a word of a record that no kernel of the launch writes, at an address all
+// lanes of the wave share: one scalar load, and no vector register
+template <typename T>
+__device__ __forceinline__ T sload(const T &v) {
+  return *(const T __attribute__((address_space(4))) *)(uintptr_t)&v;
+}
+
+// ---------------------------------------------------------------------------
+// lanes of one group of G (aligned) exchange values by DPP
+// ---------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const unsigned long long b = dbits(v);
+  const uint32_t lo = dpp_u32<CTRL>((uint32_t)b), hi = dpp_u32<CTRL>((uint32_t)(b >> 32));
+  return bitsd(((unsigned long long)hi << 32) | lo);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_SHR1 = 0x111,
+              DPP_SHR2 = 0x112, DPP_SHR4 = 0x114;
+// sum over the group, the same bits in every lane (each step adds the same
+// two partial sums in either order)
+template <int G>
+__device__ __forceinline__ double group_sum(double v) {
+  v += dpp_f64<DPP_XOR1>(v);
+  if (G >= 4) v += dpp_f64<DPP_XOR2>(v);
+  if (G == 8) v += dpp_f64<DPP_HALF_MIRROR>(v);
+  return v;
+}
+template <int G>
+__device__ __forceinline__ uint32_t group_or(uint32_t v) {
+  v |= dpp_u32<DPP_XOR1>(v);
+  if (G >= 4) v |= dpp_u32<DPP_XOR2>(v);
+  if (G == 8) v |= dpp_u32<DPP_HALF_MIRROR>(v);
+  return v;
+}
+// inclusive prefix sum over the group's lanes (gl the lane in the group)
+template <int G>
+__device__ __forceinline__ uint32_t group_scan(uint32_t v, int gl) {
+  uint32_t t = dpp_u32<DPP_SHR1>(v);
+  v += gl >= 1 ? t : 0u;
+  if (G >= 4) {
+    t = dpp_u32<DPP_SHR2>(v);
+    v += gl >= 2 ? t : 0u;
+  }
+  if (G == 8) {
+    t = dpp_u32<DPP_SHR4>(v);
+    v += gl >= 4 ? t : 0u;
+  }
+  return v;
+}
+
+
 // Jobs a launch of k_nbr_group covers: a block works on particles of one job,
 // so that the job's record is uniform.  One job is passed by value; several
 // are looked up by their first block.
@@ -1412,7 +1353,7 @@ __device__ __forceinline__ void span_of(const Spans &sp, int b, int pb, int &job
 // hits collect in the particle's LDS ring in the order of their places, in
 // whole blocks to memory, and the pair sums read them there.  Loops end with
 // the longest list of the wave and run without divergence.  PN: geometries
-// whose patches need pair normals (pair_sums).
+// whose patches need pair normals (group_sums).
 //
 // With one lane per particle a launch of few particles leaves most of the chip
 // idle behind one long serial chain per lane, and a launch of many waits for
@@ -1434,8 +1375,8 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
     uint32_t *__restrict__ nnb, typename Vec4<R>::T *__restrict__ ap,
     double *__restrict__ dbg_gam, double *__restrict__ dbg_vt, Parts home, Spans sp) {
   static_assert(MODE == 0 || (MODE == 1 && !FORCES) || MODE == 2, "candidate list modes");
-  static_assert(G == 1 || G == 2 || G == 4 || G == 8, "a group divides a list block");
-  static_assert(MODE != 1 || G >= 4, "the list build copies with four lanes");
+  static_assert(G == 4 || G == 8 || (G == 2 && MODE == 2), "two lanes filter Verlet lists only");
+  static_assert(!PN || (D == 3 && FORCES), "pair normals: patches in 3D");
   using R4 = typename Vec4<R>::T;
   constexpr int PB = BLOCK / G;        // particles per block
   constexpr int Q = 4;                 // places per lane and pass
@@ -1443,7 +1384,7 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
   // list entries kept in LDS per particle: the lists of most waves whole
   constexpr int RL = D == 2 ? (G == 8 ? 64 : 32) : (G == 8 ? 128 : 64);
   static_assert(RL >= 2 * WIN, "room for a pass beside what waits to be stored");
-  constexpr bool RUNS = G <= 2;        // a lane takes Q consecutive places (else G lanes take G)
+  constexpr bool RUNS = G == 2;        // a lane takes Q consecutive places (else G lanes take G)
   constexpr int NS = 2 + 2 * D;        // sums per particle
   constexpr int NB = 4;                // entries per lane and pass of the sums
   constexpr uint32_t GM = (1u << G) - 1u;
@@ -1540,10 +1481,6 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
             if (G == 8) w[gl] = rg[0];
             if (G == 4) reinterpret_cast<uint2 *>(w)[gl] = make_uint2(rg[0], rg[1]);
             if (G == 2) reinterpret_cast<uint4 *>(w)[gl] = make_uint4(rg[0], rg[1], rg[2], rg[3]);
-            if (G == 1) {
-              reinterpret_cast<uint4 *>(w)[0] = make_uint4(rg[0], rg[1], rg[2], rg[3]);
-              reinterpret_cast<uint4 *>(w)[1] = make_uint4(rg[4], rg[5], rg[6], rg[7]);
-            }
           }
         }
         if (stored > upto) stored = upto;
@@ -1592,7 +1529,7 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
           uint32_t nh = 0;
 #pragma unroll
           for (int q = 0; q < Q; ++q) nh += hits[q] ? 1u : 0u;
-          const uint32_t other = G == 2 ? dpp_u32<DPP_XOR1>(nh) : 0u;
+          const uint32_t other = dpp_u32<DPP_XOR1>(nh);
           uint32_t k = count + (gl ? other : 0u);
 #pragma unroll
           for (int q = 0; q < Q; ++q)
@@ -1704,8 +1641,8 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
                 len = je > jb ? je - jb : 0u;
               }
             }
-            const uint32_t incl = G == 1 ? len : group_scan<G>(len, gl), excl = incl - len;
-            const uint32_t total = G == 1 ? len : (uint32_t)__shfl((int)incl, (int)((threadIdx.x & 63u) | (G - 1)));
+            const uint32_t incl = group_scan<G>(len, gl), excl = incl - len;
+            const uint32_t total = (uint32_t)__shfl((int)incl, (int)((threadIdx.x & 63u) | (G - 1)));
             // row r of the non-empty ones holds the places from its start on:
             // its place t is slot rowb[r + 1] + t
             const uint32_t ne = group_bits(len != 0u);
@@ -1716,21 +1653,16 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
             for (uint32_t w0 = 0; any_lane(w0 < total); w0 += WIN) {
               const uint32_t sb = excl - w0;
               const uint32_t mine = len != 0u && sb < (uint32_t)WIN ? 1u << (sb & 31u) : 0u;
-              const uint32_t starts = G == 1 ? mine : group_or<G>(mine);
+              const uint32_t starts = group_or<G>(mine);
               uint32_t jr[Q], tg[Q];
               bool cand[Q];
               float4 xr[Q];
 #pragma unroll
               for (int q = 0; q < Q; ++q) {
-                uint32_t k;   // rows started up to this place
-                if constexpr (RUNS) {
-                  k = before + __popc(starts & ((2u << (gl * Q + q)) - 1u));
-                } else {
-                  const uint32_t f = starts >> (q * G) & GM;
-                  k = before + __popc(f & le);
-                  before += __popc(f);
-                }
-                const uint32_t t = w0 + (uint32_t)(RUNS ? gl * Q + q : q * G + gl);
+                const uint32_t f = starts >> (q * G) & GM;
+                const uint32_t k = before + __popc(f & le);   // rows started up to this place
+                before += __popc(f);
+                const uint32_t t = w0 + (uint32_t)(q * G + gl);
                 const uint32_t j = rowb[col][k] + t;
                 cand[q] = t < total;
                 jr[q] = cand[q] ? j : (uint32_t)i;
@@ -1738,7 +1670,6 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
                 tg[q] = 0u;
                 xr[q] = s.xf[jr[q]];
               }
-              if constexpr (RUNS) before += __popc(starts);
               classify(xr, jr, tg, cand);
             }
           }
@@ -1783,16 +1714,14 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
         else
           group_sums<D, 1, R, CMP, PN, NB, G>(J.g, s, B.enrm, bnrow, bw, p0, klen, bscale, nbr, n, i, count, xi,
                                          pairn, S, gam, Pi, B3, lring, RL, gl);
-        if (G > 1) {
-          S = group_sum<G>(S);
-          gam = group_sum<G>(gam);
+        S = group_sum<G>(S);
+        gam = group_sum<G>(gam);
 #pragma unroll
-          for (int a = 0; a < D; ++a) Pi[a] = group_sum<G>(Pi[a]);
-          // boundary terms come up only beside the boundary
-          if (any_lane(B3[0] != 0.0 || B3[1] != 0.0 || (D == 3 && B3[2] != 0.0))) {
+        for (int a = 0; a < D; ++a) Pi[a] = group_sum<G>(Pi[a]);
+        // boundary terms come up only beside the boundary
+        if (any_lane(B3[0] != 0.0 || B3[1] != 0.0 || (D == 3 && B3[2] != 0.0))) {
 #pragma unroll
-            for (int a = 0; a < D; ++a) B3[a] = group_sum<G>(B3[a]);
-          }
+          for (int a = 0; a < D; ++a) B3[a] = group_sum<G>(B3[a]);
         }
         if (gl == 0) {
           red[0][col] = S;

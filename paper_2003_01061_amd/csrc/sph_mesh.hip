@@ -867,9 +867,9 @@ struct sph_batch {
         return launch(KID_SKIN, kern, blocks8(n), BLOCK, B, t, (const uint32_t *)cstart, 0, nbr, nnb,
                       (float4 *)nullptr, (double *)nullptr, (double *)nullptr, s, 0, n);
       };
-      return tile == 2   ? one(k_nbr_forces<2, float, false, 2, false, 1>)
-             : tile == 8 ? one(k_nbr_forces<2, float, false, 8, false, 1>)
-                         : one(k_nbr_forces<2, float, false, 4, false, 1>);
+      return tile == 2   ? one(k_nbr_forces<float, false, 2, false, 1>)
+             : tile == 8 ? one(k_nbr_forces<float, false, 8, false, 1>)
+                         : one(k_nbr_forces<float, false, 4, false, 1>);
     }
   }
 
@@ -913,9 +913,9 @@ struct sph_batch {
       };
       for (int k = 0; k < spans[SPAN_LARGE].sp.count; ++k) {
         const Span &q = h_spans[(size_t)SPAN_LARGE * jcap + k];
-        hipError_t e = tile == 2   ? one(k_nbr_forces<DD, R, true, 2, CMP, 0>, q)
-                       : tile == 8 ? one(k_nbr_forces<DD, R, true, 8, CMP, 0>, q)
-                                   : one(k_nbr_forces<DD, R, true, 4, CMP, 0>, q);
+        hipError_t e = tile == 2   ? one(k_nbr_forces<R, true, 2, CMP, 0>, q)
+                       : tile == 8 ? one(k_nbr_forces<R, true, 8, CMP, 0>, q)
+                                   : one(k_nbr_forces<R, true, 4, CMP, 0>, q);
         if (e != hipSuccess) return e;
       }
       return hipSuccess;
@@ -928,7 +928,7 @@ struct sph_batch {
     const Batch B = dev();
     const Parts &s = P[cur];
     HIPCHK((launch_nbr_forces<DD, R, CMP>(B, s)));
-    if (DD == 3)   // 3D sweep B gathers precomputed mid-point records
+    if constexpr (DD == 3)   // 3D sweep B gathers precomputed mid-point records
       HIPCHK(launch(KID_MIDPOINT, k_midpoint<DD, R>, spans[SPAN_ALL1].blocks, BLOCK, B, s, (const R4 *)ap,
                     (R4 *)mid, spans[SPAN_ALL1].sp));
     // Sweep B.  3D takes 4 lanes a particle: 8 are slower from 30,000 particles
