@@ -12,9 +12,13 @@ device-resident batches and steps them with continuous batching.
   sequence of its batch; the two batches run on their own streams, so 2D and
   3D work overlaps on the device.  After every chunk of steps the server
   reads the per-job flags, retires converged jobs (positions copied to the
-  host, latency stamped), which frees their slot and memory, and admits what
-  is waiting.  A job's particles cross the host/device boundary only at admit
-  and retire.
+  host, latency stamped) and admits what is waiting.  A job's particles cross
+  the host/device boundary only at admit and retire.  A retired job keeps its
+  slot and memory, frozen, until the next admission to its batch or until a
+  request needs them: taking it out compacts the batch and has its step graphs
+  captured again, which the admission does anyway.  Its particles still go
+  through the steps of the jobs beside it, so it is taken out as soon as they
+  cost more than that (PARK_LIMIT).
 * Latency.  Time from a request's arrival to its converged positions on the
   host; the report gives p50 / p99 beside the throughput.
 
@@ -62,12 +66,19 @@ class JobResult:
 
 @dataclass
 class ServeStats:
-    blocked_slots: int = 0      # admission rounds stopped by the slot cap
-    blocked_memory: int = 0     # ... by the particle or cell capacity
+    blocked_slots: int = 0      # admission rounds that found every slot taken, by running
+                                # jobs or by retired ones (which then give way at once)
+    blocked_memory: int = 0     # ... no room for the particles or cells
     polls: int = 0
     chunks: int = 0
     max_resident: int = 0
     max_particles: dict = field(default_factory=dict)
+
+
+# Steps x particles that retired jobs may cost a batch before they are taken out.
+# Taking them out and capturing the graphs again takes 0.5 to 1.1 ms (2 to 32 jobs),
+# 1,000,000 steps x particles of frozen jobs 0.12 ms in 2D and 0.18 ms in 3D.
+PARK_LIMIT = 4_000_000
 
 
 class _Resident:
@@ -136,6 +147,8 @@ class Server:
         results = {r.idx: JobResult(r.idx, r.dim, r.n, r.arrival) for r in reqs}
         queues = {2: deque(), 3: deque()}
         resident = {2: {}, 3: {}}
+        parked = {2: {}, 3: {}}                # retired jobs that still hold their slot and memory
+        idle = {2: 0, 3: 0}                    # steps x particles they have cost
         used = {d: [0, 0] for d in (2, 3)}     # particles, cells
         finished = 0
         nxt = 0
@@ -152,6 +165,17 @@ class Server:
                     from .autotune import with_cell_factor
                     spec_of[r.idx] = with_cell_factor(r.spec, cf)
             return spec_of[r.idx]
+
+        def reclaim(d):
+            for job, rj in parked[d].items():
+                self.batches[d].remove(job)
+                used[d][0] -= rj.req.n
+                used[d][1] -= rj.cells
+            parked[d].clear()
+            idle[d] = 0
+
+        def slots_taken():
+            return sum(len(resident[d]) + len(parked[d]) for d in (2, 3))
         t0 = self.clock()
         st = self.stats
         st.max_particles = {2: 0, 3: 0}
@@ -179,9 +203,13 @@ class Server:
                         res.message = "larger than the batch capacity" if cells >= 0 else "invalid job"
                         finished += 1
                         continue
-                    if sum(len(x) for x in resident.values()) >= self.slots:
+                    if slots_taken() >= self.slots:
                         st.blocked_slots += 1
-                        break
+                        for dd in (2, 3):
+                            reclaim(dd)
+                        if slots_taken() >= self.slots:
+                            break
+                    reclaim(d)
                     if (used[d][0] + r.n > self.cap_particles[d]
                             or used[d][1] + cells > self.cap_cells[d]):
                         st.blocked_memory += 1
@@ -207,6 +235,11 @@ class Server:
             # one chunk on every busy batch (each on its own stream), then poll
             for d in (2, 3):
                 if resident[d]:
+                    cost = self.chunk * sum(rj.req.n for rj in parked[d].values())
+                    if idle[d] + cost > PARK_LIMIT:
+                        reclaim(d)
+                    else:
+                        idle[d] += cost
                     self.batches[d].step(self.chunk)
                     st.chunks += 1
             for d in (2, 3):
@@ -231,12 +264,17 @@ class Server:
                             res.positions = x
                     except Exception as e:
                         res.status, res.message, res.done = "error", str(e), now()
-                    b.remove(job)
-                    used[d][0] -= rj.req.n
-                    used[d][1] -= rj.cells
+                    if res.status == "ok":
+                        parked[d][job] = rj
+                    else:                        # still moving, or unusable: out at once
+                        b.remove(job)
+                        used[d][0] -= rj.req.n
+                        used[d][1] -= rj.cells
                     finished += 1
                     if progress:
                         progress(res)
+        for d in (2, 3):
+            reclaim(d)
         return [results[r.idx] for r in sorted(reqs, key=lambda r: r.idx)]
 
 
