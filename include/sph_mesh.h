@@ -197,11 +197,11 @@ typedef struct {
                                 if the grid would exceed 2^29 cells */
   int32_t scan_tile;         /* candidate records tested per pass of the scan
                                 with one lane per particle: 2, 4 or 8; 0 = 4.
-                                That scan serves 2D jobs of 175,000 particles
-                                or more without Verlet lists and 2D list
-                                builds of 200,000 or more; other work takes
-                                several lanes per particle and ignores the
-                                tile.  Results do not depend on it
+                                That scan serves 2D without Verlet lists from
+                                175,000 particles in all jobs together on, and
+                                2D list builds from 200,000 on; other work
+                                takes several lanes per particle and ignores
+                                the tile.  Results do not depend on it
                                 (autotuning knob) */
   int32_t cell_levels;       /* cell grids per band of h: level l holds the
                                 particles with h_min 2^l <= h < h_min 2^(l+1)

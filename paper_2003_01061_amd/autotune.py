@@ -39,8 +39,8 @@ DEFAULT = {"cell_factor": 1.0, "scan_tile": 4, "verlet_skin": 0.0}
 CELL_FACTORS = (1.0, 0.75, 1.25)
 SCAN_TILES = (4, 2, 8)
 SKINS = (0.3, 0.5, 0.8)
-# particles from which a 2D job without Verlet lists, and the list build of a 2D
-# batch, take one lane per particle (ONE_LANE and ONE_LANE_BUILD of sph_mesh.hip)
+# particles from which a 2D batch without Verlet lists, and the list build of a
+# 2D batch, take one lane per particle (ONE_LANE and ONE_LANE_BUILD of sph_mesh.hip)
 ONE_LANE, ONE_LANE_BUILD = 175_000, 200_000
 
 
@@ -48,9 +48,7 @@ def tile_matters(specs, dim, skin):
     """Does a kernel of these jobs' step read the scan tile?"""
     if dim != 2:
         return False
-    if skin > 0.0:
-        return sum(s.n for s in specs) >= ONE_LANE_BUILD
-    return any(s.n >= ONE_LANE for s in specs)
+    return sum(s.n for s in specs) >= (ONE_LANE_BUILD if skin > 0.0 else ONE_LANE)
 
 
 @dataclass

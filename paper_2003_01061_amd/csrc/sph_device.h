@@ -307,6 +307,7 @@ struct JobDev {
   float band_in, band_out, band_reach;
   double band_x;   // for particles with coordinates up to this in magnitude
   int32_t bw, nf, live;
+  int32_t four;  // 2D: a particle's sums are added as four lanes add them (small jobs)
   int32_t vol;   // the job's volume feature (local id), -1 if none
 };
 
@@ -712,25 +713,35 @@ __host__ __device__ __forceinline__ int h_level(const Grid &G, double h) {
 // -3 (1-q/2)^2, finite at r = 0.  The intrinsic dimension K is a template
 // argument.
 // ---------------------------------------------------------------------------
+__host__ __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__host__ __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <int D, typename R>
+__host__ __device__ __forceinline__ R sum2(R x, R y, R z) {   // x^2 + y^2 (+ z^2 in 3D)
+  const R s = fma_(x, x, y * y);
+  return D == 3 ? fma_(z, z, s) : s;
+}
 template <int K, typename R>
 __host__ __device__ __forceinline__ constexpr R kalphaK() {
   return K == 1 ? R(0.625) : (K == 2 ? R(0.55704230082163367519) : R(0.41778172561622525639));
 }
 template <int K, typename R>
 __host__ __device__ __forceinline__ R wshapeK(R q) {   // w(q), caller guarantees q < 2 or clamps t
-  R t = R(1) - R(0.5) * q;
+#pragma clang fp contract(off)
+  R t = fma_(R(-0.5), q, R(1));
   t = t > R(0) ? t : R(0);
   const R t2 = t * t;
-  return K == 1 ? t2 * t * (R(1) + R(1.5) * q) : t2 * t2 * (R(1) + R(2) * q);
+  return K == 1 ? t2 * t * fma_(R(1.5), q, R(1)) : t2 * t2 * fma_(R(2), q, R(1));
 }
 template <int K, typename R>
 __host__ __device__ __forceinline__ R dwqK(R q) {      // w'(q)/q
-  R t = R(1) - R(0.5) * q;
+#pragma clang fp contract(off)
+  R t = fma_(R(-0.5), q, R(1));
   t = t > R(0) ? t : R(0);
   return K == 1 ? R(-3) * t * t : R(-5) * t * t * t;
 }
 template <int K, typename R>
 __host__ __device__ __forceinline__ R powK(R h) {
+#pragma clang fp contract(off)
   return K == 1 ? h : (K == 2 ? h * h : h * h * h);
 }
 
@@ -755,7 +766,10 @@ struct Sum<false> {
   __host__ __device__ __forceinline__ void add(T v) { s += (double)v; }
   // v x: one conversion and one FP64 multiply-add
   template <typename T>
-  __host__ __device__ __forceinline__ void add_product(T v, double x) { s += (double)v * x; }
+  __host__ __device__ __forceinline__ void add_product(T v, double x) { s = __builtin_fma((double)v, x, s); }
+  // a b in the terms' precision
+  __host__ __device__ __forceinline__ void add_term(double a, double b) { s = __builtin_fma(a, b, s); }
+  __host__ __device__ __forceinline__ void add_term(float a, float b) { s += (double)(a * b); }
   __host__ __device__ __forceinline__ double get() const { return s; }
 };
 template <>
@@ -766,11 +780,13 @@ struct Sum<true> {
     c = 0.0f;
   }
   __device__ __forceinline__ void add(float v) {
+#pragma clang fp contract(off)
     const float t = s + v;
     c += __builtin_fabsf(s) >= __builtin_fabsf(v) ? (s - t) + v : (v - t) + s;
     s = t;
   }
   __device__ __forceinline__ void add_product(float v, double x) { add(v * (float)x); }
+  __device__ __forceinline__ void add_term(float a, float b) { add(a * b); }
   __device__ __forceinline__ double get() const { return (double)s + (double)c; }
 };
 
@@ -781,6 +797,7 @@ struct Sum<true> {
 // the tangent part on a curve, zero on a singular point
 template <int D>
 __host__ __device__ __forceinline__ void tangent(const Geom &g, const Feat &F, const double *x, double *u) {
+#pragma clang fp contract(off)
   switch (F.kind) {
     case K_VOL: return;
     case K_BOXSIDE: u[F.axis] = 0.0; return;
@@ -893,6 +910,7 @@ __host__ __device__ __forceinline__ void tangent(const Geom &g, const Feat &F, c
 template <int D>
 __host__ __device__ __forceinline__ void tangent_at(const Geom &g, const Feat &F, const double *x,
                                            const double4 *__restrict__ enrm, int i, double *u) {
+#pragma clang fp contract(off)
   if (F.kind == K_POLY) {
     const double4 e = enrm[i];
     if (D == 2) {   // e is the right normal (t1, -t0)

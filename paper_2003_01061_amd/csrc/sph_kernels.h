@@ -552,6 +552,10 @@ __global__ __launch_bounds__(BLOCK, 8) void k_rank_gather(Batch B, int n, const 
   }
 }
 
+// how the kernels with one lane per particle add (2D): in list order, as four
+// lanes would, or either by the job (JobDev::four)
+enum { AS_ONE, AS_FOUR, AS_JOB };
+
 // does v hold in a lane of the wave (on the host: a lane by itself)
 __host__ __device__ __forceinline__ bool any_lane(bool v) {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -567,13 +571,112 @@ using LdsList = const uint32_t *;
 #endif
 
 // ---------------------------------------------------------------------------
-// Pair sums of sweep A (Eqs. (gamma_disc_renormSPH), (particle_volume),
-// (sph_pressure_force_disc_weighted)) of particle i of intrinsic dimension K
-// over its neighbour list, by G lanes: lane l takes the entries l, l + G, ...,
-// NB of them at a time, and the caller adds the lanes' sums.  Pair terms are
+// Pair terms of sweep A (Eqs. (gamma_disc_renormSPH), (particle_volume),
+// (sph_pressure_force_disc_weighted)) for a particle of intrinsic dimension K,
 // evaluated in R and accumulated by Sum<CMP>: in FP64, or (CMP, R = float) in
-// FP32 with Neumaier compensation.
+// FP32 with Neumaier compensation.  What is fused into a multiply-add is written
+// out, not left to the compiler, so that every kernel gets the same bits: group_sums
+// by four lanes and four_sums, which add them in the same order, take each other's
+// place.
 // ---------------------------------------------------------------------------
+template <int D, int K, typename R, bool CMP>
+struct TermsA {
+  // h enters rho_t = h^-k; the kernel is evaluated at the smoothing length
+  // klen h (cut-off radius 2 klen h)
+  R hi, kl, ihi, hik, hi2k, ihik, P0;
+  __host__ __device__ __forceinline__ TermsA(double h, double klen, double p0) {
+#pragma clang fp contract(off)
+    hi = (R)h;
+    kl = (R)klen;
+    ihi = rcp_((R)(klen * h));
+    hik = powK<K>(hi);
+    hi2k = hik * hik;
+    ihik = powK<K>(ihi);
+    P0 = (R)p0;
+  }
+  // the self term, when `on`
+  __host__ __device__ __forceinline__ void self(bool on, Sum<CMP> &aS, Sum<CMP> &aG) const {
+#pragma clang fp contract(off)
+    constexpr R alpha = kalphaK<K, R>();
+    const R wself = alpha * ihik;
+    aS.init(on ? (double)wself : 0.0);
+    aG.init(on ? (double)(wself * hik) : 0.0);
+  }
+  // a neighbour of the same feature, with no weight unless `on`
+  __host__ __device__ __forceinline__ void own(const double4 &xi, const double4 &xj, bool on, Sum<CMP> &aS,
+                                               Sum<CMP> &aG, Sum<CMP> *aP) const {
+#pragma clang fp contract(off)
+    constexpr R alpha = kalphaK<K, R>();
+    const double d0 = xi.x - xj.x, d1 = xi.y - xj.y, d2 = D == 3 ? xi.z - xj.z : 0.0;
+    const R dx0 = (R)d0, dx1 = (R)d1, dx2 = D == 3 ? (R)d2 : R(0);
+    const R rr = sqrt_(sum2<D>(dx0, dx1, dx2));
+    const R hj = (R)xj.w;
+    const R hjk = powK<K>(hj);
+    const R hsum = fma_(hjk, hjk, hi2k);
+    const R ihij = rcp_(kl * (R(0.5) * (hi + hj)));
+    const R qij = rr * ihij;
+    const R w = on ? alpha * wshapeK<K>(rr * ihi) * ihik : R(0);           // W(r, h_i)
+    aS.add(w);
+    aG.add_term(w, hjk);
+    const R ih2 = ihij * ihij;
+    const R ihk2 = K == 1 ? ih2 * ihij : (K == 2 ? ih2 * ih2 : ih2 * ih2 * ihij);
+    const R c = on ? P0 * hsum * alpha * dwqK<K>(qij) * ihk2 : R(0);       // (dW/dr)/r at h_ij
+    aP[0].add_product(c, d0);
+    aP[1].add_product(c, d1);
+    if (D == 3) aP[2].add_product(c, d2);
+  }
+  // the boundary particle b; false where the normal is the pair's own (3D
+  // patches, modes 7 and 8), which is left to the pass for those
+  __host__ __device__ __forceinline__ bool boundary(const Parts &s, const double4 *__restrict__ enrm,
+                                                    const BNorm *__restrict__ bnrow, int bw, double bscale,
+                                                    const double4 &xi, uint32_t b, Sum<CMP> &aS,
+                                                    Sum<CMP> *aB) const {
+#pragma clang fp contract(off)
+    constexpr R alpha = kalphaK<K, R>();
+    const double4 xj = s.xh[b];
+    const R dx0 = (R)(xi.x - xj.x), dx1 = (R)(xi.y - xj.y);
+    const R dx2 = D == 3 ? (R)(xi.z - xj.z) : R(0);
+    const R rr = sqrt_(sum2<D>(dx0, dx1, dx2));
+    // the particle volume (Eq. (particle_volume)) is the inverse of i's
+    // number density: the boundary particles that act on i count too
+    aS.add(alpha * wshapeK<K>(rr * ihi) * ihik);
+    double nv[3];
+    if constexpr (K == D) {   // the volume: the domain's normal k_rank_gather stored at b
+      const double4 e4 = enrm[b];
+      nv[0] = e4.x;
+      nv[1] = e4.y;
+      nv[2] = e4.z;
+    } else {
+      const BNorm N = bnrow[s.f[b] & (MAXF - 1)];
+      if (D == 3 && N.mode >= 7) return false;
+      if (N.mode >= 2) {   // a curved boundary: the normal k_rank_gather stored
+        const double4 e4 = enrm[b];
+        nv[0] = e4.x;
+        nv[1] = e4.y;
+        nv[2] = e4.z;
+      } else {
+        nv[0] = N.n[0];
+        nv[1] = N.n[1];
+        nv[2] = N.n[2];
+      }
+    }
+    const R hj = (R)xj.w;
+    const R hjk = powK<K>(hj);
+    const R hsum = fma_(hjk, hjk, hi2k);
+    const R ihij = rcp_(kl * (R(0.5) * (hi + hj)));
+    const R om = (bw == 0 ? rcp_(hj) : (bw == 1 ? powK<K>(hj) * rcp_(hj) : R(0))) * (R)bscale;
+    const R w = alpha * wshapeK<K>(rr * ihij) * powK<K>(ihij);          // W(r, h_ib)
+    const R c = P0 * hsum * w * om;
+    aB[0].add_product(c, nv[0]);
+    aB[1].add_product(c, nv[1]);
+    if (D == 3) aB[2].add_product(c, nv[2]);
+    return true;
+  }
+};
+
+// Pair sums of sweep A of particle i over its neighbour list, by G lanes: lane l
+// takes the entries l, l + G, ..., NB of them at a time, and the caller adds the
+// lanes' sums.
 template <int D, int K, typename R, bool CMP, bool PN, int NB, int G>
 __host__ __device__ __forceinline__ void group_sums(const Geom &g, const Parts &s,
                                              const double4 *__restrict__ enrm,
@@ -583,20 +686,9 @@ __host__ __device__ __forceinline__ void group_sums(const Geom &g, const Parts &
                                              uint32_t cnt, const double4 &xi, bool pair_normals,
                                              double &S, double &gam, double Pi[3], double B[3],
                                              LdsList ring, uint32_t ring_len, uint32_t lane) {
-  // h enters rho_t = h^-k; the kernel is evaluated at the smoothing length
-  // klen h (cut-off radius 2 klen h)
-  const R hi = (R)xi.w;
-  const R kl = (R)klen;
-  const R ihi = rcp_((R)(klen * xi.w));
-  constexpr R alpha = kalphaK<K, R>();
-  const R hik = powK<K>(hi), hi2k = hik * hik;
-  const R ihik = powK<K>(ihi);
-  const R P0 = (R)p0;
-  const R wself = alpha * ihik;
-  // the self term is lane 0's
+  const TermsA<D, K, R, CMP> T(xi.w, klen, p0);
   Sum<CMP> aS, aG, aP[3], aB[3];
-  aS.init(lane == 0 ? (double)wself : 0.0);
-  aG.init(lane == 0 ? (double)(wself * hik) : 0.0);
+  T.self(lane == 0, aS, aG);   // the self term is lane 0's
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     aP[a].init(0.0);
@@ -640,68 +732,14 @@ __host__ __device__ __forceinline__ void group_sums(const Geom &g, const Parts &
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       if (q > 0 && !any_lane(e0 + q * G + lane < cnt)) break;   // no list of the wave goes on
-      const double4 xj = xr[q];
-      const double d0 = xi.x - xj.x, d1 = xi.y - xj.y, d2 = D == 3 ? xi.z - xj.z : 0.0;
-      const R dx0 = (R)d0, dx1 = (R)d1, dx2 = D == 3 ? (R)d2 : R(0);
-      const R rr = sqrt_(dx0 * dx0 + dx1 * dx1 + dx2 * dx2);
-      const R hj = (R)xj.w;
-      const R hjk = powK<K>(hj);
-      const R hsum = hi2k + hjk * hjk;
-      const R ihij = rcp_(kl * (R(0.5) * (hi + hj)));
-      const R qij = rr * ihij;
-      const R w = own[q] ? alpha * wshapeK<K>(rr * ihi) * ihik : R(0);           // W(r, h_i)
-      aS.add(w);
-      aG.add(w * hjk);
-      const R ih2 = ihij * ihij;
-      const R ihk2 = K == 1 ? ih2 * ihij : (K == 2 ? ih2 * ih2 : ih2 * ih2 * ihij);
-      const R c = own[q] ? P0 * hsum * alpha * dwqK<K>(qij) * ihk2 : R(0);       // (dW/dr)/r at h_ij
-      aP[0].add_product(c, d0);
-      aP[1].add_product(c, d1);
-      if (D == 3) aP[2].add_product(c, d2);
+      T.own(xi, xr[q], own[q], aS, aG, aP);
     }
   }
   if (boundary) {
     for (uint32_t e = lane; e < cnt; e += G) {
       const uint32_t v = entry(e);
       if (!(v >> 31)) continue;
-      const uint32_t b = v & 0x7fffffffu;
-      const double4 xj = s.xh[b];
-      const R dx0 = (R)(xi.x - xj.x), dx1 = (R)(xi.y - xj.y);
-      const R dx2 = D == 3 ? (R)(xi.z - xj.z) : R(0);
-      const R rr = sqrt_(dx0 * dx0 + dx1 * dx1 + dx2 * dx2);
-      // the particle volume (Eq. (particle_volume)) is the inverse of i's
-      // number density: the boundary particles that act on i count too
-      aS.add(alpha * wshapeK<K>(rr * ihi) * ihik);
-      double nv[3];
-      if constexpr (K == D) {   // the volume: the domain's normal k_rank_gather stored at b
-        const double4 e4 = enrm[b];
-        nv[0] = e4.x;
-        nv[1] = e4.y;
-        nv[2] = e4.z;
-      } else {
-        const BNorm N = bnrow[s.f[b] & (MAXF - 1)];
-        if (D == 3 && N.mode >= 7) continue;   // normal of the pair: the pass below
-        if (N.mode >= 2) {   // a curved boundary: the normal k_rank_gather stored
-          const double4 e4 = enrm[b];
-          nv[0] = e4.x;
-          nv[1] = e4.y;
-          nv[2] = e4.z;
-        } else {
-          nv[0] = N.n[0];
-          nv[1] = N.n[1];
-          nv[2] = N.n[2];
-        }
-      }
-      const R hj = (R)xj.w;
-      const R hjk = powK<K>(hj);
-      const R hsum = hi2k + hjk * hjk;
-      const R ihij = rcp_(kl * (R(0.5) * (hi + hj)));
-      const R om = (bw == 0 ? rcp_(hj) : (bw == 1 ? powK<K>(hj) * rcp_(hj) : R(0))) * (R)bscale;
-      const R w = alpha * wshapeK<K>(rr * ihij) * powK<K>(ihij);          // W(r, h_ib)
-      const R c = P0 * hsum * w * om;
-      aB[0].add_product(c, nv[0]);
-      aB[1].add_product(c, nv[1]);
-      if (D == 3) aB[2].add_product(c, nv[2]);
+      (void)T.boundary(s, enrm, bnrow, bw, bscale, xi, v & 0x7fffffffu, aS, aB);
     }
   }
   if constexpr (D == 3 && K == 2) {
@@ -738,11 +776,11 @@ __host__ __device__ __forceinline__ void group_sums(const Geom &g, const Parts &
         const double il = l > 0.0 ? 1.0 / l : 0.0;
         const R hj = (R)xj.w;
         const R hjk = powK<K>(hj);
-        const R hsum = hi2k + hjk * hjk;
-        const R ihij = rcp_(kl * (R(0.5) * (hi + hj)));
+        const R hsum = T.hi2k + hjk * hjk;
+        const R ihij = rcp_(T.kl * (R(0.5) * (T.hi + hj)));
         const R om = (bw == 0 ? rcp_(hj) : (bw == 1 ? powK<K>(hj) * rcp_(hj) : R(0))) * (R)bscale;
-        const R w = alpha * wshapeK<K>(rr * ihij) * powK<K>(ihij);      // W(r, h_ib)
-        const R c = P0 * hsum * w * om;
+        const R w = kalphaK<K, R>() * wshapeK<K>(rr * ihij) * powK<K>(ihij);      // W(r, h_ib)
+        const R c = T.P0 * hsum * w * om;
         aB[0].add_product(c, d0 * il);
         aB[1].add_product(c, d1 * il);
         aB[2].add_product(c, d2 * il);
@@ -758,7 +796,7 @@ __host__ __device__ __forceinline__ void group_sums(const Geom &g, const Parts &
   }
 }
 
-// The same sums by the one lane of k_nbr_forces (2D), in list order.  With
+// The sums by one lane in list order, each entry's terms as they come (2D).  With
 // nlanes > 1, and in 3D, which has no such kernel: those of lane `lane` of
 // k_nbr_group (host callers).
 template <int D, int K, typename R, bool CMP>
@@ -906,6 +944,103 @@ __host__ __device__ __forceinline__ void sweep_a_sums(const Geom &g, const Parts
   Pi[2] = B[2] = 0.0;
 }
 
+// The sums of group_sums by one lane for four (2D): entry e in sum e % 4, own
+// entries first, then the boundary's, and the four added as group_sum adds the
+// lanes'.  Same bits, in the registers of one lane.
+template <int K, typename R, bool CMP>
+__host__ __device__ __forceinline__ void four_sums(const Parts &s, const double4 *__restrict__ enrm,
+                                                   const BNorm *__restrict__ bnrow, int bw, double p0, double klen,
+                                                   double bscale, const uint32_t *__restrict__ nbr, int n, int i,
+                                                   uint32_t cnt, const double4 &xi, double &S, double &gam,
+                                                   double Pi[3], double B[3], const uint32_t *ring,
+                                                   uint32_t ring_len, uint32_t ring_stride) {
+  constexpr int D = 2, V = 4;
+  auto total = [](const Sum<CMP> &a, const Sum<CMP> &b, const Sum<CMP> &c, const Sum<CMP> &d) {
+    return (a.get() + b.get()) + (c.get() + d.get());
+  };
+  const TermsA<D, K, R, CMP> T(xi.w, klen, p0);
+  Sum<CMP> aS[V], aG[V], aP[V][3];
+#pragma unroll
+  for (int l = 0; l < V; ++l) {
+    T.self(l == 0, aS[l], aG[l]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) aP[l][a].init(0.0);
+  }
+  constexpr int NB = SPH_NBATCH;
+  static_assert((NB == 4 || NB == LB) && NB % V == 0, "record batches of 4 or 8 tile a list block");
+  // records gathered together: GB of a batch's NB (fewer live registers)
+  constexpr int GB = SPH_GBATCH < NB ? SPH_GBATCH : NB;
+  static_assert(NB % GB == 0, "gather groups tile a batch");
+  // The list's last entries may also sit in the caller's LDS ring (entry e
+  // in slot e % ring_len, column stride ring_stride): entries from lbase on
+  // are read there, the ones before from the list in memory (whole blocks,
+  // as lbase is a multiple of LB).  Either way every entry is read in list
+  // order, so the sums are the same.
+  uint32_t lbase = cnt;
+  if (ring != nullptr) lbase = cnt > ring_len ? (cnt - ring_len + LB - 1) / LB * LB : 0u;
+  const uint4 *gl = reinterpret_cast<const uint4 *>(nbr) + (size_t)i * (LB / 4);
+  auto batch = [&](uint32_t e0, uint32_t (&u)[NB]) {
+    if (e0 < lbase) {   // NB entries of a block in memory: 16-byte loads
+#pragma unroll
+      for (int h = 0; h < NB / 4; ++h) {
+        const uint4 w = gl[(size_t)(e0 / LB) * n * (LB / 4) + (e0 % LB) / 4 + h];
+        u[4 * h] = w.x;
+        u[4 * h + 1] = w.y;
+        u[4 * h + 2] = w.z;
+        u[4 * h + 3] = w.w;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NB; ++q) u[q] = ring[((e0 + q) % ring_len) * ring_stride];
+    }
+#pragma unroll
+    for (int q = 0; q < NB; ++q) u[q] = e0 + q < cnt ? u[q] : 0u;
+  };
+  uint32_t boundary = 0u;   // its top bit: some entry is of the boundary
+  for (uint32_t e0 = 0; e0 < cnt; e0 += NB) {
+    uint32_t u[NB];
+    batch(e0, u);
+#pragma unroll
+    for (int g0 = 0; g0 < NB; g0 += GB) {
+      double4 xr[GB];
+#pragma unroll
+      for (int q = 0; q < GB; ++q) xr[q] = s.xh[u[g0 + q] & 0x7fffffffu];
+#pragma unroll
+      for (int q = 0; q < GB; ++q) {
+        if (e0 + g0 + q >= cnt) break;
+        const uint32_t v = u[g0 + q];
+        boundary |= v;
+        T.own(xi, xr[q], !(v >> 31), aS[(g0 + q) % V], aG[(g0 + q) % V], aP[(g0 + q) % V]);
+      }
+    }
+  }
+  gam = total(aG[0], aG[1], aG[2], aG[3]);
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    Pi[a] = total(aP[0][a], aP[1][a], aP[2][a], aP[3][a]);
+    B[a] = 0.0;
+  }
+  if (boundary >> 31) {
+    Sum<CMP> aB[V][3];
+#pragma unroll
+    for (int l = 0; l < V; ++l)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) aB[l][a].init(0.0);
+    for (uint32_t e0 = 0; e0 < cnt; e0 += NB) {
+      uint32_t u[NB];
+      batch(e0, u);
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        if (u[q] >> 31)
+          (void)T.boundary(s, enrm, bnrow, bw, bscale, xi, u[q] & 0x7fffffffu, aS[q % V], aB[q % V]);
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a) B[a] = total(aB[0][a], aB[1][a], aB[2][a], aB[3][a]);
+  }
+  S = total(aS[0], aS[1], aS[2], aS[3]);
+  Pi[2] = B[2] = 0.0;
+}
+
 // Appends the hits among tag[0, NB) (0xffffffff: no hit) to a particle's
 // column of the LDS ring (slot k at rc[k * stride], slot = entry mod LR) and
 // stores each list block they complete to *wp as two 16-byte writes, while
@@ -970,6 +1105,42 @@ __device__ __forceinline__ void band_beyond(const JobDev &J, const double4 &xi, 
   cout = (float)((1.0 + w) * (1.0 + w) * k * k);
 }
 
+// a word of a record that no kernel of the launch writes, at an address all
+// lanes of the wave share: one scalar load, and no vector register
+template <typename T>
+__device__ __forceinline__ T sload(const T &v) {
+  return *(const T __attribute__((address_space(4))) *)(uintptr_t)&v;
+}
+
+// Jobs that a launch covers: a block works on particles of one job,
+// so that the job's record is uniform.  One job is passed by value; several
+// are looked up by their first block.
+static_assert(MAXJ <= 64, "a lane per span");
+struct Span {
+  int block, job, first, end;   // first block; the job's slot; its particles' slots
+};
+struct Spans {
+  int count;
+  Span one;
+  const Span *tab;
+};
+__device__ __forceinline__ void span_of(const Spans &sp, int b, int pb, int &job, int &first, int &end) {
+  Span s = sp.one;
+  if (sp.count > 1) {   // the last span that starts at b or before: a lane per span
+    const int l = __lane_id();
+    const bool at = l < sp.count && sp.tab[l].block <= b;
+    const int k = __popcll(__builtin_amdgcn_ballot_w64(at)) - 1;
+    const Span *t = sp.tab + k;
+    s.block = sload(t->block);
+    s.job = sload(t->job);
+    s.first = sload(t->first);
+    s.end = sload(t->end);
+  }
+  job = s.job;
+  first = s.first + (b - s.block) * pb;
+  end = s.end;
+}
+
 // ---------------------------------------------------------------------------
 // neighbour list (Algorithm 1 "construct Verlet neighbor list") and, in the
 // same launch, sweep A over it; FORCES = false builds lists only.  Two kernels
@@ -981,30 +1152,35 @@ __device__ __forceinline__ void band_beyond(const JobDev &J, const double4 &xi, 
 // per neighbour instead of once per candidate.  Every particle reads its own
 // job's geometry and grid; cells of different jobs never meet.
 //
-// k_nbr_forces: one lane per particle of the slots [i0, i1).  It is the faster
-// for large 2D jobs (launch_nbr_forces), whose short lists do not fill several
-// lanes: of 1,000,000 particles, FP32, cell scan, 119 us against 135 with 2
-// lanes and 157 with 4; the list build 170 against 225 us.
+// k_nbr_forces: one lane per particle, a block on particles of one job.  It is the
+// faster for large 2D batches (small_job, launch_build), whose short lists do not
+// fill several lanes: of 1,000,000 particles, FP32, cell scan, 117 us against 135
+// with 2 lanes and 148 with 4; the list build 170 against 225 us.
 // MODE 0: candidates from the cell scan, as above.  MODE 1 (FORCES = false,
 // only when a rebuild is due): the Verlet candidate list of every
 // non-singular particle, the cell scan at the reach (c + delta) h with the
 // FP32 test alone, widened by its error bound so that it keeps every pair
 // within that reach.
 // ---------------------------------------------------------------------------
-template <typename R, bool FORCES, int NB, bool CMP, int MODE>
-__global__ __launch_bounds__(BLOCK) void k_nbr_forces(
+template <typename R, bool FORCES, int NB, bool CMP, int MODE, int SUMS>
+__global__ __launch_bounds__(BLOCK, SUMS != AS_ONE && sizeof(R) == 8 ? 4 : 1) void k_nbr_forces(
     Batch B, Parts s, const uint32_t *__restrict__ cstart, int all, uint32_t *__restrict__ nbr,
     uint32_t *__restrict__ nnb, typename Vec4<R>::T *__restrict__ ap,
-    double *__restrict__ dbg_gam, double *__restrict__ dbg_vt, Parts home, int i0, int i1) {
+    double *__restrict__ dbg_gam, double *__restrict__ dbg_vt, Parts home, Spans sp) {
   constexpr int D = 2;
   static_assert(MODE == 0 || (MODE == 1 && !FORCES), "candidate list modes");
   if (MODE == 1) {
     if (B.vstate[VS_REBUILD] == 0ull) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) B.vstate[VS_BUILDS] += 1ull;
+  }
+  // the block's job and its particles [first, end)
+  int job, first, end;
+  span_of(sp, xcd_block(), BLOCK, job, first, end);
+  if (MODE == 1) {
     // s holds the particles just sorted; they go back to the buffer the
     // steps use between rebuilds (no kernel of this launch reads it)
-    const int c = i0 + xcd_block() * BLOCK + (int)threadIdx.x;
-    if (c < i1) {
+    const int c = first + (int)threadIdx.x;
+    if (c < end) {
       home.xh[c] = s.xh[c];
       home.v[c] = s.v[c];
       home.f[c] = s.f[c];
@@ -1025,14 +1201,13 @@ __global__ __launch_bounds__(BLOCK) void k_nbr_forces(
   __shared__ uint32_t ring[LR][BLOCK];
   const int col = (int)threadIdx.x;
   const int n = B.n;
-  const int i = i0 + xcd_block() * BLOCK + (int)threadIdx.x;
+  const int i = first + (int)threadIdx.x;
   bool act = false;
-  int fi = 0, job = 0;
+  int fi = 0;
   unsigned long long dtb = ~0ull, vfix = 0ull, mine = 0ull;
-  if (i < i1) {
+  const JobDev &J = B.jobs[job];
+  if (i < end) {
     fi = s.f[i];
-    job = fi / MAXF;
-    const JobDev &J = B.jobs[job];
     const Feat F = B.feat[fi];
     const bool moving = F.type != T_SI && B.grp[fi].active;
     const bool want = F.type != T_SI && (all || MODE == 1 || B.grp[fi].active);
@@ -1177,12 +1352,22 @@ __global__ __launch_bounds__(BLOCK) void k_nbr_forces(
       }
       const BNorm *bnrow = B.bn + (size_t)fi * MAXF;
       double S, gam, Pi[3], B3[3];
-      if (k == D)
-        sweep_a_sums<D, D, R, CMP>(J.g, s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, fi, false, S, gam, Pi, B3,
-                                        LDS_SUMS ? &ring[0][col] : nullptr, LR, BLOCK);
-      else
-        sweep_a_sums<D, 1, R, CMP>(J.g, s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, fi, false, S, gam, Pi, B3,
-                                        LDS_SUMS ? &ring[0][col] : nullptr, LR, BLOCK);
+      const uint32_t *rg = LDS_SUMS ? &ring[0][col] : nullptr;
+      if (SUMS == AS_FOUR || (SUMS == AS_JOB && J.four)) {
+        if (k == D)
+          four_sums<D, R, CMP>(s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, S, gam, Pi, B3,
+                               rg, LR, BLOCK);
+        else
+          four_sums<1, R, CMP>(s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, S, gam, Pi, B3,
+                               rg, LR, BLOCK);
+      } else {
+        if (k == D)
+          sweep_a_sums<D, D, R, CMP>(J.g, s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, fi,
+                                     false, S, gam, Pi, B3, rg, LR, BLOCK);
+        else
+          sweep_a_sums<D, 1, R, CMP>(J.g, s, B.enrm, bnrow, J.bw, J.p0, J.klen, J.bscale, nbr, n, i, count, xi, fi,
+                                     false, S, gam, Pi, B3, rg, LR, BLOCK);
+      }
       // the FP32 modes store a^p in FP32 and hold V~ and the time steps to
       // 1e-5: FP32 reciprocals and roots suffice there (relative error 2^-23)
       constexpr bool F32 = sizeof(R) == 4;
@@ -1205,8 +1390,7 @@ __global__ __launch_bounds__(BLOCK) void k_nbr_forces(
       if (dbg_vt) dbg_vt[i] = vt;
       // Eq. (fa_time_step_size) terms from a^p and v^n
       const double rc = J.ksup * xi.w;
-      const double dt = step_terms<F32>(rc, a3[0] * a3[0] + a3[1] * a3[1] + a3[2] * a3[2],
-                                        v4.x * v4.x + v4.y * v4.y + v4.z * v4.z);
+      const double dt = step_terms<F32>(rc, sum2<3>(a3[0], a3[1], a3[2]), sum2<3>(v4.x, v4.y, v4.z));
       dtb = dbits(dt);
       vfix = (unsigned long long)__builtin_llrint(vt * B.grp[fi].vscale);
     } else if (FORCES) {
@@ -1225,7 +1409,7 @@ __global__ __launch_bounds__(BLOCK) void k_nbr_forces(
   }
   if (FORCES) {
     wave_commit(act, fi, dtb, vfix, B.smin, DT1, B.ssum);
-    wave_count(i < i1 && mine != 0ull, job, mine, B.scnt, SC_PAIRS);
+    wave_count(i < end && mine != 0ull, job, mine, B.scnt, SC_PAIRS);
   }
 }
 
@@ -1248,13 +1432,6 @@ __host__ __device__ __forceinline__ void row_range(int whole, float frac, float 
   t1 = whole + (int)__builtin_floorf(frac + w);
   t0 = t0 > 0 ? (t0 < nc - 1 ? t0 : nc - 1) : 0;
   t1 = t1 > 0 ? (t1 < nc - 1 ? t1 : nc - 1) : 0;
-}
-
-// a word of a record that no kernel of the launch writes, at an address all
-// lanes of the wave share: one scalar load, and no vector register
-template <typename T>
-__device__ __forceinline__ T sload(const T &v) {
-  return *(const T __attribute__((address_space(4))) *)(uintptr_t)&v;
 }
 
 // ---------------------------------------------------------------------------
@@ -1304,35 +1481,6 @@ __device__ __forceinline__ uint32_t group_scan(uint32_t v, int gl) {
   return v;
 }
 
-
-// Jobs a launch of k_nbr_group covers: a block works on particles of one job,
-// so that the job's record is uniform.  One job is passed by value; several
-// are looked up by their first block.
-static_assert(MAXJ <= 64, "a lane per span");
-struct Span {
-  int block, job, first, end;   // first block; the job's slot; its particles' slots
-};
-struct Spans {
-  int count;
-  Span one;
-  const Span *tab;
-};
-__device__ __forceinline__ void span_of(const Spans &sp, int b, int pb, int &job, int &first, int &end) {
-  Span s = sp.one;
-  if (sp.count > 1) {   // the last span that starts at b or before: a lane per span
-    const int l = __lane_id();
-    const bool at = l < sp.count && sp.tab[l].block <= b;
-    const int k = __popcll(__builtin_amdgcn_ballot_w64(at)) - 1;
-    const Span *t = sp.tab + k;
-    s.block = sload(t->block);
-    s.job = sload(t->job);
-    s.first = sload(t->first);
-    s.end = sload(t->end);
-  }
-  job = s.job;
-  first = s.first + (b - s.block) * pb;
-  end = s.end;
-}
 
 // ---------------------------------------------------------------------------
 // neighbour list (Algorithm 1 "construct Verlet neighbor list") and, in the
@@ -1786,8 +1934,7 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_
       vt = F32 ? (double)rcp_((float)S) : 1.0 / S;
       // Eq. (fa_time_step_size) terms from a^p and v^n
       const double rc = J.ksup * xp.w;
-      dtb = dbits(step_terms<F32>(rc, a3[0] * a3[0] + a3[1] * a3[1] + a3[2] * a3[2],
-                                  v4.x * v4.x + v4.y * v4.y + v4.z * v4.z));
+      dtb = dbits(step_terms<F32>(rc, sum2<3>(a3[0], a3[1], a3[2]), sum2<3>(v4.x, v4.y, v4.z)));
       vfix = (unsigned long long)__builtin_llrint(vt * B.grp[fp].vscale);
     }
     ap[p] = o;
@@ -1865,8 +2012,9 @@ __global__ __launch_bounds__(BLOCK) void k_midpoint(Batch B, Parts s,
 // A lane alone reads half a block of its list at a time, and in FP32 leaves the
 // loop and skips boundary entries by itself, which gathers less (1,000,000
 // particles in 2D: 53.5 us, all lanes together 56); the FP64 sums lose by that
-// (96.8 against 94).
-template <int D, int K, typename R, bool MID, bool CMP, int G>
+// (96.8 against 94).  FOUR: entry e in sum e % 4, as four lanes add them, with the
+// multiply-adds written out as in TermsA.
+template <int D, int K, typename R, bool MID, bool CMP, int G, bool FOUR>
 __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4<R>::T *__restrict__ ap,
                                              const typename Vec4<R>::T *__restrict__ mid,
                                              const uint32_t *__restrict__ nbr, int n, int i,
@@ -1884,11 +2032,15 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
   const R halfR = (R)half;
   constexpr bool XF = sizeof(R) == 4;
   const float3 xfi = make_float3((float)xi.x, (float)xi.y, (float)xi.z);
-  Sum<CMP> aF[3];
+  static_assert(!FOUR || G == 1, "one lane for four");
+  constexpr int V = FOUR ? 4 : 1;   // entry e in sum e % 4, as four lanes add them
+  Sum<CMP> aF[V][3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) aF[a].init(0.0);
+  for (int l = 0; l < V; ++l)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) aF[l][a].init(0.0);
   constexpr int NB = 4;
-  static_assert(LB % NB == 0, "half a block at a time");
+  static_assert(LB % NB == 0 && NB % V == 0, "half a block at a time");
   constexpr bool ALONE = G == 1 && sizeof(R) == 4;
   for (uint32_t e0 = 0; ALONE ? e0 < cnt : any_lane(e0 < cnt); e0 += NB * G) {
     uint32_t u[NB];
@@ -1938,7 +2090,7 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
         dx2 = D == 3 ? (R)(xi.z - xj.z) : R(0);
         hj = (R)xj.w;
       }
-      const R rr = sqrt_(dx0 * dx0 + dx1 * dx1 + dx2 * dx2);
+      const R rr = sqrt_(sum2<D>(dx0, dx1, dx2));
       const R hjk = powK<K>(hj);
       R vtj[3], etaj;
       if (MID) {
@@ -1949,10 +2101,10 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
       } else {   // 2D: {a^p_x, a^p_y, v_x, v_y} in the sweep precision
         static_assert(MID || D == 2, "the a^p record carries v only in 2D");
         const R4 apj = mr[q];
-        vtj[0] = apj.z + halfR * apj.x;
-        vtj[1] = apj.w + halfR * apj.y;
+        vtj[0] = fma_(halfR, apj.x, apj.z);
+        vtj[1] = fma_(halfR, apj.y, apj.w);
         vtj[2] = R(0);
-        const R vmj = sqrt_(vtj[0] * vtj[0] + vtj[1] * vtj[1] + vtj[2] * vtj[2]);
+        const R vmj = sqrt_(sum2<2>(vtj[0], vtj[1], R(0)));
         etaj = nuf * hj * vmj * rcp_(hjk);
       }
       const R es = etai + etaj;
@@ -1960,13 +2112,15 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
       const R ihij = rcp_(kl * (R(0.5) * (hi + hj)));
       const R ih2 = ihij * ihij;
       const R ihk2 = K == 1 ? ih2 * ihij : (K == 2 ? ih2 * ih2 : ih2 * ih2 * ihij);
-      const R c = H * (hi2k + hjk * hjk) * alpha * dwqK<K>(rr * ihij) * ihk2;
+      const R c = H * fma_(hjk, hjk, hi2k) * alpha * dwqK<K>(rr * ihij) * ihk2;
 #pragma unroll
-      for (int a = 0; a < D; ++a) aF[a].add(c * (vtiR[a] - vtj[a]));
+      for (int a = 0; a < D; ++a) aF[q % V][a].add_term(c, vtiR[a] - vtj[a]);
     }
   }
 #pragma unroll
-  for (int a = 0; a < 3; ++a) Fv[a] = aF[a].get();
+  for (int a = 0; a < 3; ++a)
+    Fv[a] = V == 1 ? aF[0][a].get()
+                   : (aF[0][a].get() + aF[1 % V][a].get()) + (aF[2 % V][a].get() + aF[3 % V][a].get());
 }
 
 // ---------------------------------------------------------------------------
@@ -1981,8 +2135,8 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
 // (small_job).  The gathers want waves: of 2,000,000 particles in 3D 296 us with
 // 86 registers (5 waves a SIMD), 267 with 80 (6), 420 with 72, which spill.
 // ---------------------------------------------------------------------------
-template <int D, typename R, bool CMP, int G>
-__global__ __launch_bounds__(BLOCK, sizeof(R) == 4 ? 6 : 4) void k_sweep_b(Batch B, Parts s,
+template <int D, typename R, bool CMP, int G, int SUMS>
+__global__ __launch_bounds__(BLOCK, sizeof(R) == 4 ? (SUMS == AS_ONE ? 6 : 5) : 4) void k_sweep_b(Batch B, Parts s,
                                                    const uint32_t *__restrict__ nbr,
                                                    const uint32_t *__restrict__ nnb,
                                                    const typename Vec4<R>::T *__restrict__ ap,
@@ -2006,9 +2160,9 @@ __global__ __launch_bounds__(BLOCK, sizeof(R) == 4 ? 6 : 4) void k_sweep_b(Batch
     api[0] = (double)a4.x;
     api[1] = (double)a4.y;
     api[2] = D == 3 ? (double)a4.z : 0.0;
-    vt[0] = v4.x + half * api[0];
-    vt[1] = v4.y + half * api[1];
-    vt[2] = v4.z + half * api[2];
+    vt[0] = fma_(half, api[0], v4.x);
+    vt[1] = fma_(half, api[1], v4.y);
+    vt[2] = fma_(half, api[2], v4.z);
   };
   const int i = first + col;
   const int fi = i < end ? (int)s.f[i] : job * MAXF;
@@ -2025,16 +2179,27 @@ __global__ __launch_bounds__(BLOCK, sizeof(R) == 4 ? 6 : 4) void k_sweep_b(Batch
       double api[3], vti[3];
       midpoint(i, half, s.v[i], api, vti);
       if (gl == 0) halves[col] = half;
-      const double vmi = __builtin_sqrt(vti[0] * vti[0] + vti[1] * vti[1] + vti[2] * vti[2]);
+      const double vmi = __builtin_sqrt(sum2<3>(vti[0], vti[1], vti[2]));
       const uint32_t cnt = nnb[i];
       const double klen = sload(J.klen);
       double fv[3];
-      if (k == D)
-        sweep_b_sums<D, D, R, D == 3, CMP, G>(s, ap, mid, nbr, B.n, i, cnt, xi, vti, vmi, half, klen, fv, gl);
-      else if (k == D - 1)
-        sweep_b_sums<D, D - 1, R, D == 3, CMP, G>(s, ap, mid, nbr, B.n, i, cnt, xi, vti, vmi, half, klen, fv, gl);
-      else
-        sweep_b_sums<D, 1, R, D == 3, CMP, G>(s, ap, mid, nbr, B.n, i, cnt, xi, vti, vmi, half, klen, fv, gl);
+      bool four = false;
+      if constexpr (SUMS != AS_ONE) {
+        static_assert(D == 2 && G == 1, "one lane for four");
+        four = SUMS == AS_FOUR || J.four;
+        if (four && k == D)
+          sweep_b_sums<D, D, R, false, CMP, 1, true>(s, ap, mid, nbr, B.n, i, cnt, xi, vti, vmi, half, klen, fv, gl);
+        else if (four)
+          sweep_b_sums<D, 1, R, false, CMP, 1, true>(s, ap, mid, nbr, B.n, i, cnt, xi, vti, vmi, half, klen, fv, gl);
+      }
+      if (!four) {
+        if (k == D)
+          sweep_b_sums<D, D, R, D == 3, CMP, G, false>(s, ap, mid, nbr, B.n, i, cnt, xi, vti, vmi, half, klen, fv, gl);
+        else if (k == D - 1)
+          sweep_b_sums<D, D - 1, R, D == 3, CMP, G, false>(s, ap, mid, nbr, B.n, i, cnt, xi, vti, vmi, half, klen, fv, gl);
+        else
+          sweep_b_sums<D, 1, R, D == 3, CMP, G, false>(s, ap, mid, nbr, B.n, i, cnt, xi, vti, vmi, half, klen, fv, gl);
+      }
 #pragma unroll
       for (int a = 0; a < D; ++a) {
         if constexpr (G > 1) fv[a] = group_sum<G>(fv[a]);
@@ -2074,13 +2239,12 @@ __global__ __launch_bounds__(BLOCK, sizeof(R) == 4 ? 6 : 4) void k_sweep_b(Batch
       const double vi[3] = {vp.x, vp.y, vp.z};
       double a3[3];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) a3[a] = api[a] + fv[a] - eps * vi[a];
+      for (int a = 0; a < 3; ++a) a3[a] = fma_(-eps, vi[a], api[a] + fv[a]);
       o.x = (R)a3[0];
       o.y = (R)a3[1];
       o.z = (R)a3[2];
       const double rc = J.ksup * xp.w;
-      const double dt = step_terms<sizeof(R) == 4>(rc, a3[0] * a3[0] + a3[1] * a3[1] + a3[2] * a3[2],
-                                                   vt[0] * vt[0] + vt[1] * vt[1] + vt[2] * vt[2]);
+      const double dt = step_terms<sizeof(R) == 4>(rc, sum2<3>(a3[0], a3[1], a3[2]), sum2<3>(vt[0], vt[1], vt[2]));
       dtb = dbits(dt);
     }
     acc[p] = o;

@@ -22,6 +22,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/sph_mesh.h"
@@ -763,8 +764,8 @@ struct sph_batch {
            : k == SPAN_ALL4 || k == SPAN_NBR4 || k == SPAN_CURVED4 ? 4
            : k == SPAN_ALL1                                        ? 1
            : k == SPAN_NBR2                                        ? 2
-           : k == SPAN_SMALL || k == SPAN_CURVED_SMALL             ? (D == 3 ? 8 : 4)
-                                                                   : (D == 3 ? 4 : 1);
+           : k == SPAN_SMALL || k == SPAN_CURVED_SMALL             ? 8
+                                                                   : 4;
   }
   bool in_span(int k, const HostJob &J) const {
     if (k <= SPAN_ALL1) return true;
@@ -777,25 +778,31 @@ struct sph_batch {
   SpanSet spans[SPAN_SETS];
   std::vector<Span> h_spans;   // host copy of the tables
   bool lists_long = false;     // a resident job has long lists
+  int sums = AS_FOUR;          // how one lane per particle adds (2D)
 
-  // Does a job take the neighbour kernel for small jobs?  The choice is by the
-  // job's own size and reach, never the batch's, so that a job's sums are added
-  // in the same order alone and in any mix.  More lanes per particle shorten the
-  // chain that bounds a job too small to fill the chip; fewer lose less to the
-  // lists' last places.  Cell scan and sums, FP32, us per launch.  3D, 8 against
-  // 4 lanes: 30,000 particles 36 / 49, 200,000 128 / 125, 400,000 229 / 215,
-  // 800,000 447 / 408; with a reach of 2.5h, whose lists do not fit 4 lanes'
-  // LDS, 400,000 368 / 427.  2D, 4 lanes against one, FP32 and FP64: 50,000
-  // 17.7 / 25.6 and 18.6 / 28.1, 100,000 23.5 / 27.2 and 26.0 / 31.5, 150,000
-  // 29.5 / 31.4 and 33.2 / 36.8, 200,000 35.8 / 32.9 and 40.3 / 39.4, 250,000 42.2
-  // / 33.8 and 47.5 / 41.4, 300,000 49.1 / 50.1 and 55.6 / 57.7, 400,000 61.0 / 56.7
-  // and 68.9 / 67.1, 1,000,000 148 / 117 and 166 / 143.  (Of the one-lane blocks
-  // 1,024 run at once: 262,144 particles fill the chip, a few more begin a
-  // second round.)  Sweep B in 2D, the same: 50,000 9.5 / 11.1 and 12.4 / 15.2,
-  // 100,000 12.4 / 13.0 and 18.6 / 19.8, 150,000 15.8 / 15.6 and 24.9 / 25.2,
-  // 200,000 19.2 / 16.9 and 31.1 / 29.2, 250,000 22.8 / 17.8 and 37.6 / 31.4,
-  // 1,000,000 71.9 / 53.5 and 134 / 94; 2 lanes 18.0, 20.1, 59 and 28.5, 32.4, 106
-  // at the last three sizes.
+  // Small jobs.  A job's sums are added in an order that its own size and reach
+  // choose, never the batch's, so that it gets the same bits alone and in any mix.
+  // 3D: the order is the kernel's, 8 lanes per particle for small jobs, 4 for the
+  // others.  More lanes shorten the chain that bounds a job too small to fill the
+  // chip; fewer lose less to the lists' last places.  Cell scan and sums, FP32,
+  // us per launch, 8 against 4 lanes: 30,000 particles 36 / 49, 200,000 128 / 125,
+  // 400,000 229 / 215, 800,000 447 / 408; with a reach of 2.5h, whose lists do not
+  // fit 4 lanes' LDS, 400,000 368 / 427.
+  // 2D: small jobs add as four lanes do, the others in list order, and the kernel
+  // follows the batch: below ONE_LANE particles in all four lanes per particle, from
+  // there on one lane, which adds as four where the job asks for it.  Four lanes
+  // against one, us per launch, FP32 and FP64: 50,000 particles 17.7 / 25.6 and 18.6
+  // / 28.1, 100,000 23.5 / 27.2 and 26.0 / 31.5, 150,000 29.5 / 31.4 and 33.2 / 36.8,
+  // 200,000 35.8 / 32.9 and 40.3 / 39.4, 250,000 42.2 / 33.8 and 47.5 / 41.4, 300,000
+  // 49.1 / 50.1 and 55.6 / 57.7, 400,000 61.0 / 56.7 and 68.9 / 67.1, 1,000,000 148 /
+  // 117 and 166 / 143.  (Of the one-lane blocks 1,024 run at once: 262,144 particles
+  // fill the chip, a few more begin a second round.)  Sweep B, the same: 50,000 9.5 /
+  // 11.1 and 12.4 / 15.2, 100,000 12.4 / 13.0 and 18.6 / 19.8, 150,000 15.8 / 15.6 and
+  // 24.9 / 25.2, 200,000 19.2 / 16.9 and 31.1 / 29.2, 250,000 22.8 / 17.8 and 37.6 /
+  // 31.4, 1,000,000 71.9 / 53.5 and 134 / 94.  One lane as four: a batch of 16 jobs of
+  // 64,000 308 us a step, by four lanes 354 (FP64 397, 450); of a job of 1,000,000
+  // the scan takes 123 us instead of 117 (FP64 156, 143), so large jobs keep the
+  // list's order.
   static constexpr int ONE_LANE = 175000;
   static bool long_lists(const HostJob &J) { return J.dev.ksup > 2.25; }
   bool small_job(const HostJob &J) const {
@@ -809,7 +816,12 @@ struct sph_batch {
       if (jobs[j].live && jobs[j].n > 0) order.push_back(j);
     std::sort(order.begin(), order.end(), [&](int x, int y) { return jobs[x].cbase < jobs[y].cbase; });
     lists_long = false;
-    for (int j : order) lists_long = lists_long || long_lists(jobs[j]);
+    int small = 0;
+    for (int j : order) {
+      lists_long = lists_long || long_lists(jobs[j]);
+      small += small_job(jobs[j]) ? 1 : 0;
+    }
+    sums = small == 0 ? AS_ONE : small == (int)order.size() ? AS_FOUR : AS_JOB;
     h_spans.assign((size_t)SPAN_SETS * jcap, Span{});
     for (int k = 0; k < SPAN_SETS; ++k) {
       const int pb = BLOCK / span_lanes(k);
@@ -863,13 +875,9 @@ struct sph_batch {
       return group(k_nbr_group<3, float, false, false, 1, 4, false>, spans[SPAN_ALL4]);
     } else {
       if (n < ONE_LANE_BUILD) return group(k_nbr_group<2, float, false, false, 1, 4, false>, spans[SPAN_ALL4]);
-      auto one = [&](auto kern) {
-        return launch(KID_SKIN, kern, blocks8(n), BLOCK, B, t, (const uint32_t *)cstart, 0, nbr, nnb,
-                      (float4 *)nullptr, (double *)nullptr, (double *)nullptr, s, 0, n);
-      };
-      return tile == 2   ? one(k_nbr_forces<float, false, 2, false, 1>)
-             : tile == 8 ? one(k_nbr_forces<float, false, 8, false, 1>)
-                         : one(k_nbr_forces<float, false, 4, false, 1>);
+      return tile == 2   ? group(k_nbr_forces<float, false, 2, false, 1, AS_ONE>, spans[SPAN_ALL1])
+             : tile == 8 ? group(k_nbr_forces<float, false, 8, false, 1, AS_ONE>, spans[SPAN_ALL1])
+                         : group(k_nbr_forces<float, false, 4, false, 1, AS_ONE>, spans[SPAN_ALL1]);
     }
   }
 
@@ -900,26 +908,28 @@ struct sph_batch {
         return group(k_nbr_group<2, R, true, CMP, 2, 2, false>, SPAN_NBR2);
       }
     }
-    if (hipError_t e = group(k_nbr_group<DD, R, true, CMP, 0, DD == 3 ? 8 : 4, false>, SPAN_SMALL)) return e;
     if constexpr (DD == 3) {
+      if (hipError_t e = group(k_nbr_group<3, R, true, CMP, 0, 8, false>, SPAN_SMALL)) return e;
       if (hipError_t e = group(k_nbr_group<3, R, true, CMP, 0, 4, false>, SPAN_LARGE)) return e;
       if (hipError_t e = group(k_nbr_group<3, R, true, CMP, 0, 8, true>, SPAN_CURVED_SMALL)) return e;
       return group(k_nbr_group<3, R, true, CMP, 0, 4, true>, SPAN_CURVED_LARGE);
     } else {
-      // one lane per particle, a launch per large job
-      auto one = [&](auto kern, const Span &q) {
-        return launch(KID_NBR_FORCES, kern, blocks8(q.end - q.first), BLOCK, B, s, (const uint32_t *)cstart,
-                      0, nbr, nnb, (R4 *)ap, dbg_gam, dbg_vt, s, q.first, q.end);
-      };
-      for (int k = 0; k < spans[SPAN_LARGE].sp.count; ++k) {
-        const Span &q = h_spans[(size_t)SPAN_LARGE * jcap + k];
-        hipError_t e = tile == 2   ? one(k_nbr_forces<R, true, 2, CMP, 0>, q)
-                       : tile == 8 ? one(k_nbr_forces<R, true, 8, CMP, 0>, q)
-                                   : one(k_nbr_forces<R, true, 4, CMP, 0>, q);
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
+      if (n < ONE_LANE) return group(k_nbr_group<2, R, true, CMP, 0, 4, false>, SPAN_NBR4);
+      return by_sums([&](auto how) {
+        constexpr int S = decltype(how)::value;
+        return tile == 2   ? group(k_nbr_forces<R, true, 2, CMP, 0, S>, SPAN_ALL1)
+               : tile == 8 ? group(k_nbr_forces<R, true, 8, CMP, 0, S>, SPAN_ALL1)
+                           : group(k_nbr_forces<R, true, 4, CMP, 0, S>, SPAN_ALL1);
+      });
     }
+  }
+
+  // f with the resident jobs' way of adding by one lane
+  template <typename F>
+  hipError_t by_sums(F f) {
+    return sums == AS_ONE    ? f(std::integral_constant<int, AS_ONE>())
+           : sums == AS_FOUR ? f(std::integral_constant<int, AS_FOUR>())
+                             : f(std::integral_constant<int, AS_JOB>());
   }
 
   template <int DD, typename R, bool CMP = false>
@@ -933,17 +943,19 @@ struct sph_batch {
                     (R4 *)mid, spans[SPAN_ALL1].sp));
     // Sweep B.  3D takes 4 lanes a particle: 8 are slower from 30,000 particles
     // on (2,000,000: 404 against 290 us), 2 below (66,000: 28 against 20).  2D
-    // takes 4 for small jobs (2,503 particles: 7.2 us, 2 lanes 9.6) and one for
-    // large ones (small_job has both).
+    // takes 4 (2,503 particles: 7.2 us, 2 lanes 9.6), or one from ONE_LANE on.
     auto sweep_b = [&](auto kern, const SpanSet &S) {
       return launch(KID_SWEEP_B, kern, S.blocks, BLOCK, B, s, (const uint32_t *)nbr, (const uint32_t *)nnb,
                     (const R4 *)ap, (const R4 *)mid, (R4 *)acc, dbg_vm, S.sp);
     };
     if constexpr (DD == 3) {
-      HIPCHK(sweep_b(k_sweep_b<DD, R, CMP, 4>, spans[SPAN_ALL4]));
+      HIPCHK(sweep_b(k_sweep_b<3, R, CMP, 4, AS_ONE>, spans[SPAN_ALL4]));
+    } else if (n < ONE_LANE) {
+      HIPCHK(sweep_b(k_sweep_b<2, R, CMP, 4, AS_ONE>, spans[SPAN_ALL4]));
     } else {
-      HIPCHK(sweep_b(k_sweep_b<DD, R, CMP, 4>, spans[SPAN_SMALL]));
-      HIPCHK(sweep_b(k_sweep_b<DD, R, CMP, 1>, spans[SPAN_LARGE]));
+      HIPCHK(by_sums([&](auto how) {
+        return sweep_b(k_sweep_b<2, R, CMP, 1, decltype(how)::value>, spans[SPAN_ALL1]);
+      }));
     }
     HIPCHK(launch(KID_INTEGRATE_HASH, k_integrate_hash<DD, R>, spans[SPAN_ALL1].blocks, BLOCK, B, s,
                   (const R4 *)acc, cell, rank, cnt, spans[SPAN_ALL1].sp));
@@ -1567,6 +1579,7 @@ extern "C" sph_status sph_batch_add(sph_batch *b, const sph_geometry *g, const s
   if (slot < 0) return fail(SPH_ERR_OUT_OF_MEMORY, "no free job slot (max_jobs %d)", b->jcap);
   HostJob J;
   fill_job(J, g, s, p, b->ncell, (int)n);
+  J.dev.four = b->D == 2 && b->small_job(J) ? 1 : 0;
   set_skin(J.dev, b->skin);
   if ((int64_t)b->n + n > b->ncap)
     return fail(SPH_ERR_OUT_OF_MEMORY, "particle capacity %d exceeded", b->ncap);

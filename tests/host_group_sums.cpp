@@ -4,7 +4,8 @@
 // mode (constant, stored, and the pair normals of 3D patches at curves and
 // vertices), lists of 0 to 61 entries read from the ring or from memory, split
 // over 1, 2, 4 and 8 lanes, the lanes' sums add up to the sums written out below
-// in long double from the equations.
+// in long double from the equations; and one lane that adds as four (four_sums,
+// 2D) gets the four lanes' sums bit for bit.
 //
 // Bar: a sum of n <= 62 terms of about 20 roundings each, added in another
 // order, differs by at most (20 + 62) 2^-53 of the sum of the terms' magnitudes,
@@ -180,6 +181,36 @@ static bool split(const Problem &P, const Sums &want, uint32_t ring_len, bool pa
   return true;
 }
 
+// four_sums against the four lanes of group_sums, added as group_sum adds them
+template <int K>
+static bool four(const Problem &P, uint32_t ring_len) {
+  Geom g{};
+  g.cpts = P.cpts.data();
+  Parts s{};
+  s.xh = const_cast<double4 *>(P.xh.data());
+  s.f = const_cast<uint16_t *>(P.f.data());
+  double lane[4][8];
+  for (uint32_t l = 0; l < 4; ++l)
+    group_sums<2, K, double, false, false, 4, 4>(g, s, P.enrm.data(), P.bn.data(), P.bw, P.p0, P.klen, P.bscale,
+                                                 P.nbr.data(), P.n, P.i, P.cnt, P.xh[P.i], false, lane[l][0],
+                                                 lane[l][1], lane[l] + 2, lane[l] + 5, (LdsList)P.ring.data(),
+                                                 ring_len, l);
+  for (int source = 0; source < 2; ++source) {   // from memory; with the list's end in the ring
+    double got[8];
+    four_sums<K, double, false>(s, P.enrm.data(), P.bn.data(), P.bw, P.p0, P.klen, P.bscale, P.nbr.data(), P.n, P.i,
+                                P.cnt, P.xh[P.i], got[0], got[1], got + 2, got + 5,
+                                source ? P.ring.data() : nullptr, ring_len, 1);
+    for (int k = 0; k < 8; ++k) {
+      const double want = (lane[0][k] + lane[1][k]) + (lane[2][k] + lane[3][k]);
+      if (got[k] != want) {
+        std::printf("k %d as four, %u entries: sum %d is %.17g, want %.17g\n", K, P.cnt, k, got[k], want);
+        return false;
+      }
+    }
+  }
+  return true;
+}
+
 template <int D, int K>
 static long run(std::mt19937_64 &rng, int trials) {
   long done = 0;
@@ -192,6 +223,8 @@ static long run(std::mt19937_64 &rng, int trials) {
     if (!split<D, K, 1>(P, want, ring_len, pk) || !split<D, K, 2>(P, want, ring_len, pk) ||
         !split<D, K, 4>(P, want, ring_len, pk) || !split<D, K, 8>(P, want, ring_len, pk))
       return -1;
+    if constexpr (D == 2)
+      if (!four<K>(P, ring_len)) return -1;
     done += 4;
   }
   return done;

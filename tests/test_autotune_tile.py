@@ -25,7 +25,7 @@ def test_the_lines_are_the_librarys():
 
 @pytest.mark.parametrize("dim,sizes,scan,lists", [
     (3, [2_000_000], False, False), (2, [174_999], False, False), (2, [175_000], True, False),
-    (2, [100_000, 100_000], False, True), (2, [199_999], True, False), (2, [200_000], True, True),
+    (2, [100_000, 100_000], True, True), (2, [199_999], True, False), (2, [200_000], True, True),
     (2, [1000] * 8, False, False)])
 def test_equal_configurations_are_timed_once(dim, sizes, scan, lists, monkeypatch):
     specs = [Spec(n) for n in sizes]

@@ -14,7 +14,8 @@ def test_group_sums_on_the_host(tmp_path):
     if not os.path.exists(HIPCC):
         pytest.skip("hipcc not available")
     exe = tmp_path / "host_group_sums"
-    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-fuse-cuid=none", "-Wl,--defsym=__hip_fatbin=0",
+                    "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
                     "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
                     "-Xarch_host", "-fno-sanitize-recover=all",
                     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
