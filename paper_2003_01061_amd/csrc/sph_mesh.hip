@@ -809,7 +809,8 @@ struct sph_batch {
     return D == 3 ? J.n < 200000 || long_lists(J) : J.n < ONE_LANE;
   }
 
-  // tables of the resident jobs; call when they or their slots have changed
+  // tables of the resident jobs; call when they or their slots have changed, and
+  // wait for the stream before the next change
   sph_status update_spans() {
     std::vector<int> order;
     for (int j = 0; j < njobs; ++j)
@@ -844,7 +845,6 @@ struct sph_batch {
     if (order.size() < 2) return SPH_OK;   // a kernel takes a single job's span by value
     HIPCHK(hipMemcpyAsync(d_spans, h_spans.data(), sizeof(Span) * h_spans.size(), hipMemcpyHostToDevice,
                           stream));
-    HIPCHK(hipStreamSynchronize(stream));
     return SPH_OK;
   }
 

@@ -76,7 +76,7 @@ class ServeStats:
 
 
 # Steps x particles that retired jobs may cost a batch before they are taken out.
-# Taking them out and capturing the graphs again takes 0.5 to 1.1 ms (2 to 32 jobs),
+# Taking one out and capturing the graphs again takes 0.3 to 0.7 ms (2 to 32 jobs),
 # 1,000,000 steps x particles of frozen jobs 0.12 ms in 2D and 0.18 ms in 3D.
 PARK_LIMIT = 4_000_000
 
