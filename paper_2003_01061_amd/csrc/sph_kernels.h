@@ -25,7 +25,8 @@
 // A launch covers every job of a batch: particles carry a global feature id
 // (64 per job slot), every kernel reads its particle's job record, and a
 // job's cells occupy their own range of the batch's cell ids, so jobs never
-// interact and each job's result is the same alone or in any mix.
+// interact and each job's result is the same alone or in any mix (with Verlet
+// lists, whose rebuilds follow the whole batch, up to the order of its sums).
 #pragma once
 #include "sph_device.h"
 
@@ -78,8 +79,8 @@ __device__ __forceinline__ double step_terms(double rc, double a2, double v2) {
 // order independent, so the result does not depend on scheduling or on which
 // other jobs share the launch.  Atomics on one cache line follow each other
 // wherever on the line they fall, so the copies of a feature lie 512 bytes apart:
-// k_sweep_b of 1,000,000 particles in 2D takes 59 us with 32 copies so, 91 with
-// 32 copies in 2 lines (59 with 64 in 4), and as a feature's row of copies is
+// k_sweep_b of 1,000,000 particles in 2D, by two lanes, took 59 us with 32 copies
+// so, 91 with 32 copies in 2 lines (59 with 64 in 4), and as a feature's row of copies is
 // also the row of its neighbours', a block folds them all with a few loads.
 __device__ __forceinline__ size_t stripe_at(int q, int copies, int stripe) {
   return ((size_t)(q / MAXF) * copies + stripe) * MAXF + q % MAXF;
@@ -138,8 +139,8 @@ __device__ __forceinline__ unsigned long long take(unsigned long long *p, unsign
 }
 
 // Folding the copies is the consumer's: each block of the next kernel does it in
-// the shadow of its own loads, which costs it about 0.5 us, where a launch for
-// the fold costs 3 to 4 (4,352 particles: 44.0 us a step with two such launches
+// the shadow of its own loads, which costs it 0.5 to 2 us (the control beside the
+// scan 1 to 3), where a launch costs 3 to 4 (4,352 particles: 44.0 us a step with two such launches
 // and the control's, 39.3 without; 3D, 66,000: 151 and 143; 2,000,000: no
 // difference).
 // The copies of a job's features, a lane per feature and a share of the copies
@@ -1513,16 +1514,17 @@ __device__ __forceinline__ uint32_t group_scan(uint32_t v, int gl) {
 // With one lane per particle a launch of few particles leaves most of the chip
 // idle behind one long serial chain per lane, and a launch of many waits for
 // gathers that 4 waves of 120+ registers hide badly.  G lanes make the chain
-// shorter and the waves more; one job per block makes its record scalar, which
-// takes the registers to 60 to 80.  us per launch before and now: 4,352
-// particles in 2D, FP64, 25.7 / 14; 2,503, FP32, 29.4 / 14; cube minus ball with
-// the cell scan, 66,000, FP32, 238 / 78; Verlet lists of 30,000, FP64, 57 / 26
-// (their builds, a step's share, 46 / 11); 300,000 between ellipsoids 241 / 190
-// (351 / 152); 2,000,000, FP32, 684 / 529 (211 / 200).  The arithmetic of the
-// sums and the gathers bound it from 100,000 particles up, the chain of dependent
-// loads below.  The bound on the registers gives the cell scan 5 waves a SIMD
-// instead of 4 for a few spilled words: 66,000 particles 85 / 78, the ellipsoids'
-// build 172 / 152; with 6 (3D, 80 registers, 200 bytes spilled) 127 and 160.
+// shorter and the waves more; one job per block makes its record scalar.  Verlet
+// lists take 64 to 80 registers in FP32 and 80 to 96 in FP64.  us per launch before
+// and now: 4,352 particles in 2D, FP64, 25.7 / 14; 2,503, FP32, 29.4 / 14; cube
+// minus ball with the cell scan and a reach of 2.5h, 66,000, FP32, 238 / 78; Verlet
+// lists of 30,000, FP64, 57 / 26 (their builds, a step's share, 46 / 11); 300,000
+// between ellipsoids 241 / 190 (351 / 152); 2,000,000, FP32, 684 / 528 (211 / 201).
+// The arithmetic of the sums and the gathers bound it from 100,000 particles up, the
+// chain of dependent loads below.  The cell scan is bound to 96 registers, 5 waves a
+// SIMD instead of 4, for 4 spilled in 2D and 17 to 19 (72 to 80 bytes a lane) in 3D:
+// 66,000 particles 85 / 78, the ellipsoids' build 172 / 152; with 6 waves (3D, 80
+// registers, 200 bytes spilled) 127 and 160.
 // ---------------------------------------------------------------------------
 template <int D, typename R, bool FORCES, bool CMP, int MODE, int G, bool PN>
 __global__ __launch_bounds__(BLOCK, MODE == 2 && sizeof(R) == 4 ? 6 : 5) void k_nbr_group(
@@ -2081,7 +2083,8 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
     for (int q = 0; q < NB; ++q) {
       // No list of the wave goes on.  The FP64 sums, bound by their arithmetic,
       // look each time; the FP32 ones, bound by the gathers, gain more from
-      // entries that overlap (2,000,000 particles in 3D 290 us, looking 333).
+      // entries that overlap (2,000,000 particles in 3D, at 5 waves a SIMD, 290
+      // us, looking 333).
       if (sizeof(R) == 8 && q > 0 && !any_lane(e0 + q * G + lane < cnt)) break;
       if (ALONE && u[q] >> 31) continue;
       R dx0, dx1, dx2, hj;
@@ -2138,9 +2141,9 @@ __device__ __forceinline__ void sweep_b_sums(const Parts &s, const typename Vec4
 // particles, by the chain of loads.  us before (one lane in 2D, two in 3D) and
 // now: 4,352 particles in 2D, FP64, 13.6 / 7.8; 2,503, FP32, 11.3 / 7.7; 3D
 // 30,000, FP64, 20.6 / 16; 66,000, FP32, calibrated, 25 / 20; 300,000 between
-// ellipsoids 65 / 52; 2,000,000 295 / 267.  Large 2D jobs keep one lane
+// ellipsoids 65 / 52; 2,000,000 295 / 268.  Large 2D batches take one lane
 // (small_job).  The gathers want waves: of 2,000,000 particles in 3D 296 us with
-// 86 registers (5 waves a SIMD), 267 with 80 (6), 420 with 72, which spill.
+// 86 registers (5 waves a SIMD), 268 with 80 (6), 420 with 72, which spill.
 // ---------------------------------------------------------------------------
 template <int D, typename R, bool CMP, int G, int SUMS>
 __global__ __launch_bounds__(BLOCK, sizeof(R) == 4 ? (SUMS == AS_ONE ? 6 : 5) : 4) void k_sweep_b(Batch B, Parts s,
@@ -2264,9 +2267,9 @@ __global__ __launch_bounds__(BLOCK, sizeof(R) == 4 ? (SUMS == AS_ONE ? 6 : 5) : 
 // integration with feature projection (FP64 in every precision mode), then
 // h, cell and rank of every particle for the next step's sort.  Bound by memory
 // (214 bytes a particle with Verlet lists: 2,000,000 in 103 us, 4.1 TB/s), between
-// ellipsoids by the distance solves for h.  6 waves a SIMD instead of 4 (3D, 80
-// registers for 106, 12 bytes spilled): 2,000,000 116 / 103 us, 300,000 between
-// ellipsoids 85 / 78.
+// ellipsoids by the distance solves for h.  Bound to 80 registers, 6 waves a SIMD
+// (3D, 12 bytes spilled): 2,000,000 particles 103 us, with 87 registers (5 waves)
+// 109, unbound with 105 (4) 114; 300,000 between ellipsoids 78, 78 and 88.
 // ---------------------------------------------------------------------------
 template <int D, typename R>
 __global__ __launch_bounds__(BLOCK, 6) void k_integrate_hash(

@@ -942,7 +942,7 @@ struct sph_batch {
       HIPCHK(launch(KID_MIDPOINT, k_midpoint<DD, R>, spans[SPAN_ALL1].blocks, BLOCK, B, s, (const R4 *)ap,
                     (R4 *)mid, spans[SPAN_ALL1].sp));
     // Sweep B.  3D takes 4 lanes a particle: 8 are slower from 30,000 particles
-    // on (2,000,000: 404 against 290 us), 2 below (66,000: 28 against 20).  2D
+    // on (2,000,000: 404 against 290 us at 5 waves a SIMD), 2 below (66,000: 28 against 20).  2D
     // takes 4 (2,503 particles: 7.2 us, 2 lanes 9.6), or one from ONE_LANE on.
     auto sweep_b = [&](auto kern, const SpanSet &S) {
       return launch(KID_SWEEP_B, kern, S.blocks, BLOCK, B, s, (const uint32_t *)nbr, (const uint32_t *)nnb,
